@@ -18,7 +18,6 @@
 
 namespace pwl {
 hipError_t configure_build_kernels(int max_lds);
-hipError_t configure_kde_kernels(int max_lds);
 hipError_t configure_eval_kernels(int max_lds);
 }  // namespace pwl
 
@@ -100,7 +99,6 @@ pwl_status device_ready(int* dev_out, int* num_cu, int* max_lds = nullptr) {
     if (e == hipSuccess) e = pwl::configure_build_kernels(lds);
     if (e == hipSuccess) e = pwl::configure_eval_kernels(lds);
     if (e == hipSuccess) e = pwl::configure_batch_kernels(lds);
-    if (e == hipSuccess) e = pwl::configure_kde_kernels(lds);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&g_aux[dev], hipStreamNonBlocking);
     void* sp = nullptr;
     if (e == hipSuccess) e = hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch));
@@ -717,7 +715,7 @@ pwl_status pwl_kde(const pwl_table* t, int32_t mode, const void* frame, const vo
   if (st != PWL_OK) return st;
   pwl::EvalTable e{};
   if (mode == PWL_KDE_TABLE) e = eval_view(t);
-  PWL_HIP(pwl::launch_kde(e, mode, frame, hist, H, W, T, r, sigma, out, static_cast<hipStream_t>(stream)));
+  PWL_HIP(pwl::launch_kde(e, mode, frame, hist, H, W, T, r, sigma, out, num_cu, static_cast<hipStream_t>(stream)));
   return PWL_OK;
 }
 

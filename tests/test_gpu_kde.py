@@ -66,3 +66,37 @@ def test_kde_expf_modes_need_no_table():
     assert np.max(np.abs(y - O.kde_likelihood(f_h, h_h, 1, SIGMA))) <= 1e-6
     with pytest.raises(P.PWLError):
         P.pwl_kde(None, P.KDE_TABLE, f, h, 1, SIGMA)
+
+
+@pytest.mark.parametrize("H,W_,T,r", [
+    (7, 3, 1, 2),          # narrower than a thread's pixels, window wider than the image
+    (5, 66, 2, 0),         # one tap per frame
+    (9, 129, 3, 1),
+    (21, 65, 4, 3),        # frames split over four waves
+    (11, 70, 5, 4),        # a radius without a body of its own
+    (6, 131, 6, 33 - 1),   # the largest radius
+    (8209, 1, 2, 1),       # frames split over two waves
+    (16391, 5, 2, 2),      # one wave per tile
+], ids=lambda v: str(v))
+def test_kde_tile_edges(H, W_, T, r):
+    """Images that end inside a tile, a wave or a thread's four pixels, every
+    split of the frames over waves and every body by radius, against the
+    oracle: through the table within 1e-6 of the oracle on the same table
+    (each kernel value rounds to FP32, the sum is FP64), expf alike."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    f_h, h_h = W.kde_frames(max(H, 12), max(W_, 12), T, seed=6)
+    f_h, h_h = np.ascontiguousarray(f_h[:H, :W_]), np.ascontiguousarray(h_h[:, :H, :W_])
+    f_h[0, 0], h_h[:, H // 2, 0] = (0, 255, 0, 255), (255, 0, 255, 255)   # the largest differences
+    f, h = torch.from_numpy(f_h).to(dev), torch.from_numpy(h_h).to(dev)
+    sigma = (6.0, 9.5, 31.0)
+    t = P.pwl_build(O.GAUSSIAN, (1.0, 1.0), -8.0, 8.0, 200, O.OPTIMAL, O.PROJ)
+    d = P.pwl_table_download(t)
+    X, v = d["knots"].astype(np.float64), d["values"].astype(np.float64)
+    say("  kde %dx%d T=%d r=%d" % (H, W_, T, r))
+    for mode, g in ((P.KDE_TABLE, lambda u: O.evaluate(X, v, u)), (P.KDE_EXPF, None)):
+        ref = O.kde_likelihood(f_h, h_h, r, sigma, g=g) if g else O.kde_likelihood(f_h, h_h, r, sigma)
+        got = P.pwl_kde(t, mode, f, h, r, sigma).cpu().numpy()
+        assert np.max(np.abs(got - ref)) <= 1e-6
+    t.free()
