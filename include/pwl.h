@@ -11,9 +11,9 @@
  * ---------------------------------------
  *  - Point arrays (x, y, g, dx, seg) and the value arrays v_override / dv are
  *    caller-owned DEVICE memory on the current HIP device, contiguous FP32
- *    (int32 for seg).  16-byte alignment of all point arrays selects the
- *    vectorised kernels; any other alignment is accepted and served by a
- *    scalar kernel.
+ *    (int32 for seg).  Any alignment is accepted: 4-byte aligned arrays
+ *    (any float array) are read and written 16 bytes at a time, whatever
+ *    their offsets from 16-byte boundaries; others element by element.
  *  - Tables (pwl_table) and batches (pwl_batch) are opaque, owned by the
  *    library and resident in device memory; free them with the matching
  *    *_free call.
@@ -437,16 +437,16 @@ pwl_status pwl_set_locate(int32_t mode);
 int32_t pwl_get_locate(void);
 
 #define PWL_RECORDS_PACKED 0  /* one 16-byte record {x_k, v_k, slope_k, x_{k+1}} per segment (default) */
-#define PWL_RECORDS_SOA 1     /* the same fields as four arrays of N floats                        */
+#define PWL_RECORDS_SOA 1     /* v_k and slope_k as arrays of N floats; x_k from the knot array    */
 #define PWL_RECORDS_PAIRS 2   /* 8-byte {v_k, slope_k} pairs; x_k from the knot array              */
 
 /*
  * pwl_set_records - process-wide arrangement of the per-segment data that
  * pwl_eval stages in LDS (Sec. V discusses arranging the table for the
  * GPU's memory): packed records, where a point's lookup is one 12-byte LDS
- * read; structure-of-arrays, three 4-byte reads; or value/slope pairs, one
- * 8-byte read, the segment's knot coming from the knot reads of the locate
- * (the smallest image: 8 bytes per segment instead of 16).  The values are
+ * read; structure-of-arrays, three 4-byte reads (x_k from the knots, 8 bytes
+ * per segment beside them instead of 16); or value/slope pairs, one 8-byte
+ * read, the segment's knot coming from the knot reads of the locate.  The values are
  * the same, so outputs are bit-identical; the choice is a speed A/B.  The
  * fused backward, the batched kernels and pwl_kde always use packed
  * records.  Takes effect for later launches; pwl_get_records reads it back.

@@ -287,9 +287,12 @@ size_t layout(pwl::TableDev* td, char* base, int N, int K, int G) {
     off += align256(bytes);
     return p;
   };
-  td->rec = reinterpret_cast<float4*>(take(sizeof(float4) * N));
+  float4* img = reinterpret_cast<float4*>(take(sizeof(float4) * pwl::image_words(N, K)));
+  td->rec = img;
+  td->kimg = reinterpret_cast<float*>(img + N);
+  td->lo = reinterpret_cast<uint16_t*>(img + N + pwl::image_knot_words(N));
+  td->soa = reinterpret_cast<float*>(take(sizeof(float4) * pwl::image_words_soa(N, K)));
   td->knots = reinterpret_cast<float*>(take(sizeof(float) * (N + 1)));
-  td->lo = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * (K + 1)));
   td->values = reinterpret_cast<float*>(take(sizeof(float) * (N + 1)));
   td->knots64 = reinterpret_cast<double*>(take(sizeof(double) * (N + 1)));
   td->values64 = reinterpret_cast<double*>(take(sizeof(double) * (N + 1)));
@@ -301,8 +304,9 @@ size_t layout(pwl::TableDev* td, char* base, int N, int K, int G) {
 pwl::EvalTable eval_view(const pwl_table* t) {
   pwl::EvalTable e;
   e.rec = t->td.rec;
-  e.knots = t->td.knots;
+  e.knots = t->td.kimg;
   e.lo = t->td.lo;
+  e.soa = t->td.soa;
   e.meta = t->td.status;
   e.N = t->bp.N;
   e.K = t->bp.K;

@@ -37,20 +37,9 @@ namespace {
 
 using namespace stream;
 
-// The shape of a run's table as the streaming building blocks expect it (the
-// array pointers are unused: the table is already in LDS).
-__device__ __forceinline__ EvalTable run_table(const BatchRun& r) {
-  EvalTable t;
-  t.rec = nullptr;
-  t.knots = nullptr;
-  t.lo = nullptr;
-  t.meta = nullptr;
-  t.N = r.N;
-  t.K = r.K;
-  t.a32 = r.a32;
-  t.b32 = r.b32;
-  t.scale32 = r.scale32;
-  return t;
+// The shape of a run's table (its arrays are already in LDS).
+__device__ __forceinline__ TableShape run_table(const BatchRun& r) {
+  return TableShape{r.N, r.K, r.a32, r.b32, r.scale32};
 }
 
 // Copies n >= 1 16-byte words from global memory to LDS, four per thread
@@ -103,18 +92,10 @@ __device__ __forceinline__ void put_words(const ImagePrefetch<W>& p, const float
   if (n > W * bs) stage_words(src4 + W * bs, n - W * bs, dst4 + W * bs);
 }
 
-// A workgroup barrier that orders LDS accesses only: the streaming stores a
-// wave still has in flight are not waited for (__syncthreads would).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Run q of a slice: its points and its table, whose image is in LDS.  q is
 // uniform, so the descriptor comes through the scalar cache.
 struct RunView {
-  EvalTable t;
+  TableShape t;
   Smem s;
   int64_t begin, end;
 };
@@ -477,13 +458,11 @@ __global__ __launch_bounds__(256) void k_batch_dv_reduce(const float* __restrict
   }
 }
 
-// One workgroup per table: its LDS image (records, knots with NaN outside
-// 1..N-1 up to the sentinel pad, index map, zero padding to whole 16-byte
-// words) and its deepest map cell.
+// One workgroup per table: its image and its deepest map cell.
 __global__ __launch_bounds__(256) void k_batch_pack(const BatchTable* __restrict__ tabs, int32_t* __restrict__ maxc) {
   const BatchTable bt = tabs[blockIdx.x];
   const EvalTable& t = bt.t;
-  stage_table(t, nullptr, carve(bt.img, t.N, t.K, false));   // the same words a kernel stages
+  for (int w = threadIdx.x; w < bt.nvec; w += blockDim.x) bt.img[w] = t.rec[w];
   if (threadIdx.x == 0) maxc[blockIdx.x] = (int32_t)t.meta[1];
 }
 

@@ -253,7 +253,8 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, T
       run = max(run, r);
     }
   }
-  if (tid == 0) td.lo[bp.K] = (uint16_t)(N - 1);
+  for (int u = bp.K + tid; u < 8 * image_map_words(bp.K); u += kFinalizeThreads)
+    td.lo[u] = (u == bp.K) ? (uint16_t)(N - 1) : (uint16_t)0;
   if (bad) atomicOr(&s_collapsed, 1);
   if (run > 0) atomicMax(&s_maxc, run);
 
@@ -343,8 +344,14 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, T
 
   // 5. values, flags and packed records
   const bool collapsed = s_collapsed != 0;
-  if (collapsed)   // the evaluators never leave the table through an all-zero map
+  const int fw = image_soa_field_words(N), nkw = image_knot_words(N), nmw = image_map_words(bp.K);
+  float4* soa_tail = reinterpret_cast<float4*>(td.soa) + 2 * fw;   // the copies of kimg and lo
+  if (collapsed) {   // the evaluators never leave the table through an all-zero map
     for (int u = tid; u < bp.K; u += kFinalizeThreads) td.lo[u] = 0;
+    __syncthreads();
+  }
+  for (int w = tid; w < nmw; w += kFinalizeThreads)
+    soa_tail[nkw + w] = reinterpret_cast<const float4*>(td.lo)[w];
   for (int i = tid; i < n; i += kFinalizeThreads) {
     const double c = D[i];
     td.values64[i] = c;
@@ -364,6 +371,13 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, T
       r.z = __builtin_nanf("");
     }
     td.rec[k] = r;
+    td.soa[k] = r.y;
+    td.soa[4 * fw + k] = r.z;
+  }
+  for (int k = tid; k < 4 * nkw; k += kFinalizeThreads) {
+    const float x = (k < N) ? X[k] : __builtin_nanf("");
+    td.kimg[k] = x;
+    reinterpret_cast<float*>(soa_tail)[k] = x;
   }
   if (tid == 0) {
     // the density kernels may have raised DEGENERATE / NONFINITE

@@ -1,15 +1,15 @@
 // Streaming evaluation kernels (Algorithm 1, Sec. IV) for gfx950.
 //
-// Every workgroup stages the whole table in LDS once - packed records
-// {x_k, v_k, slope_k, x_{k+1}}, the interior knots (NaN padded) and the
-// uniform index map - and then streams its share of the points with 16-byte
-// non-temporal loads and stores, U vectors per thread in flight.  The path is
-// a memory-bound gather (8 bytes per point forward, 16 fused forward and
-// backward), so there is no matrix-core work: the only per-point work is the
-// map lookup, a short knot compare loop in LDS, one record read (12 of its
-// 16 bytes; the backward reads all 16) and one FMA.  The backward
-// accumulates dL/dv in LDS with FP64 atomics and writes one column of
-// per-workgroup partial sums, which k_dv_reduce adds.
+// Every workgroup copies the table's image to LDS once - the records (or
+// their values and slopes), the knots (NaN padded) and the uniform index map,
+// which the build leaves in memory as they stand in LDS - and then streams
+// its share of the points with 16-byte non-temporal loads and stores, U
+// vectors per thread in flight.  The path is a memory-bound gather (8 bytes
+// per point forward, 16 fused forward and backward), so there is no
+// matrix-core work: the only per-point work is the map lookup, a short knot
+// compare loop in LDS, one record read and one FMA.  The backward accumulates
+// dL/dv in LDS with FP64 atomics and writes one column of per-workgroup
+// partial sums, which k_dv_reduce adds.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,48 +29,59 @@ constexpr int64_t kPointsPerStagedByte = 2;             // and per byte of table
 
 using namespace stream;
 
-template <int U, class S>
-__device__ __forceinline__ void eval_fwd_body(const EvalTable& t, const S& s, const float* __restrict__ x,
-                                              float* __restrict__ y, int64_t n, int flags) {
+// A launch's flags; from bit kBlockBit on, the workgroup's size.
+constexpr int kVec = 1;      // the arrays are 4-byte aligned: 16-byte accesses
+constexpr int kSearch = 2;   // PWL_LOCATE_SEARCH
+constexpr int kBlockBit = 8;
+
+template <int U, bool ONCE, class S>
+__device__ __forceinline__ void eval_fwd_body(const EvalTable& t, const float* __restrict__ vo, const S& s,
+                                              const float* __restrict__ x, float* __restrict__ y, int64_t n,
+                                              int flags) {
+  const int nt = flags >> kBlockBit;
   const int64_t blk = blockIdx.x, nblk = gridDim.x;
-  const bool vec = (flags & 1) != 0;
-  if (flags & 2) {   // PWL_LOCATE_SEARCH
-    fwd_range<U, -1>(t, s, x, y, 0, n, vec, blk, nblk);
+  const bool vec = (flags & kVec) != 0;
+  if constexpr (ONCE) {
+    stage_once(t, vo, s);
+    __syncthreads();
+  } else {
+    stage_table(t, vo, nt, s);
+    staged();
+    lds_barrier();
+  }
+  if (flags & kSearch) {
+    fwd_range<U, -1>(t, s, x, y, 0, n, vec, blk, nblk, nt);
     return;
   }
   switch (t.meta[1]) {
     case 0:
-    case 1: fwd_range<U, 1>(t, s, x, y, 0, n, vec, blk, nblk); break;
-    case 2: fwd_range<U, 2>(t, s, x, y, 0, n, vec, blk, nblk); break;
-    case 3: fwd_range<U, 3>(t, s, x, y, 0, n, vec, blk, nblk); break;
-    case 4: fwd_range<U, 4>(t, s, x, y, 0, n, vec, blk, nblk); break;
-    default: fwd_range<U, 0>(t, s, x, y, 0, n, vec, blk, nblk); break;
+    case 1: fwd_range<U, 1>(t, s, x, y, 0, n, vec, blk, nblk, nt); break;
+    case 2: fwd_range<U, 2>(t, s, x, y, 0, n, vec, blk, nblk, nt); break;
+    case 3: fwd_range<U, 3>(t, s, x, y, 0, n, vec, blk, nblk, nt); break;
+    case 4: fwd_range<U, 4>(t, s, x, y, 0, n, vec, blk, nblk, nt); break;
+    default: fwd_range<U, 0>(t, s, x, y, 0, n, vec, blk, nblk, nt); break;
   }
 }
 
 // REC is the arrangement of the per-segment data in LDS (pwl_set_records):
-// packed records, structure of arrays, or value/slope pairs.
-template <int U, int REC>
+// packed records, structure of arrays, or value/slope pairs; ONCE: a
+// structure-of-arrays image whose sections fit in one word per thread.  Its
+// staging is the shorter one to wait for, but what keeps it apart is the
+// register allocation of the streaming loop, which the compiler decides for
+// the whole kernel: with the general staging beside it the loop takes 104
+// registers instead of 90 and runs 341 us instead of 332 at N = 1024, 2^28
+// points.
+template <int U, int REC, bool ONCE>
 __global__ __launch_bounds__(1024) void k_eval_fwd(EvalTable t, const float* __restrict__ vo,
                                                    const float* __restrict__ x,
                                                    float* __restrict__ y, int64_t n, int flags) {
   extern __shared__ float4 lds_f4[];
-  if constexpr (REC == PWL_RECORDS_SOA) {
-    const SmemSoA s = carve_soa(lds_f4, t.N, t.K);
-    stage_table(t, vo, s);
-    __syncthreads();
-    eval_fwd_body<U>(t, s, x, y, n, flags);
-  } else if constexpr (REC == PWL_RECORDS_PAIRS) {
-    const SmemPairs s = carve_pairs(lds_f4, t.N, t.K);
-    stage_table_pairs(t, vo, s);
-    __syncthreads();
-    eval_fwd_body<U>(t, s, x, y, n, flags);
-  } else {
-    const Smem s = carve(lds_f4, t.N, t.K, false);
-    stage_table(t, vo, s);
-    __syncthreads();
-    eval_fwd_body<U>(t, s, x, y, n, flags);
-  }
+  if constexpr (REC == PWL_RECORDS_SOA)
+    eval_fwd_body<U, ONCE>(t, vo, carve_soa(lds_f4, t.N), x, y, n, flags);
+  else if constexpr (REC == PWL_RECORDS_PAIRS)
+    eval_fwd_body<U, false>(t, vo, carve_pairs(lds_f4, t.N), x, y, n, flags);
+  else
+    eval_fwd_body<U, false>(t, vo, carve(lds_f4, t.N, t.K, false), x, y, n, flags);
 }
 
 template <int U, bool WY, bool WDX, bool WDV>
@@ -78,22 +89,25 @@ __global__ __launch_bounds__(1024) void k_eval_bwd(EvalTable t, const float* __r
                                                    const float* __restrict__ x,
                                                    const float* __restrict__ g,
                                                    float* __restrict__ y, float* __restrict__ dx,
-                                                   float* __restrict__ part, int64_t n, int vec) {
+                                                   float* __restrict__ part, int64_t n, int flags) {
   extern __shared__ float4 lds_f4[];
   const Smem s = carve(lds_f4, t.N, t.K, WDV);
-  stage_table(t, vo, s);
+  const int nt = flags >> kBlockBit;
+  stage_table(t, vo, nt, s);
   if (WDV)
-    for (int k = threadIdx.x; k < (t.N + 1) * s.dvc; k += blockDim.x) s.dv[k] = 0.0;
-  __syncthreads();
+    for (int k = threadIdx.x; k < (t.N + 1) * s.dvc; k += nt) s.dv[k] = 0.0;
+  staged();
+  lds_barrier();
   using B = Bwd<U, WY, WDX, WDV>;
   const int64_t blk = blockIdx.x, nblk = gridDim.x;
+  const bool vec = (flags & kVec) != 0;
   switch (t.meta[1]) {
     case 0:
-    case 1: B::template range<1>(t, s, x, g, y, dx, 0, n, vec != 0, blk, nblk); break;
-    case 2: B::template range<2>(t, s, x, g, y, dx, 0, n, vec != 0, blk, nblk); break;
-    case 3: B::template range<3>(t, s, x, g, y, dx, 0, n, vec != 0, blk, nblk); break;
-    case 4: B::template range<4>(t, s, x, g, y, dx, 0, n, vec != 0, blk, nblk); break;
-    default: B::template range<0>(t, s, x, g, y, dx, 0, n, vec != 0, blk, nblk); break;
+    case 1: B::template range<1>(t, s, x, g, y, dx, 0, n, vec, blk, nblk, nt); break;
+    case 2: B::template range<2>(t, s, x, g, y, dx, 0, n, vec, blk, nblk, nt); break;
+    case 3: B::template range<3>(t, s, x, g, y, dx, 0, n, vec, blk, nblk, nt); break;
+    case 4: B::template range<4>(t, s, x, g, y, dx, 0, n, vec, blk, nblk, nt); break;
+    default: B::template range<0>(t, s, x, g, y, dx, 0, n, vec, blk, nblk, nt); break;
   }
   if (WDV) {
     // This workgroup's dL/dv becomes column `col` of the partial sums
@@ -101,10 +115,10 @@ __global__ __launch_bounds__(1024) void k_eval_bwd(EvalTable t, const float* __r
     // Workgroups are dealt to the 8 XCDs round-robin, so the columns are
     // ordered XCD by XCD: the workgroups of one XCD fill whole cache lines
     // in their own L2.
-    __syncthreads();
+    lds_barrier();
     const int G = gridDim.x, b = blockIdx.x;
     const int col = (G % kXcds == 0) ? (b % kXcds) * (G / kXcds) + b / kXcds : b;
-    for (int k = threadIdx.x; k <= t.N; k += blockDim.x) {
+    for (int k = threadIdx.x; k <= t.N; k += nt) {
       double acc = s.dv[k * s.dvc];
       for (int j = 1; j < s.dvc; ++j) acc += s.dv[k * s.dvc + j];   // the copies, in a fixed order
       part[(int64_t)k * G + col] = (float)acc;
@@ -153,9 +167,10 @@ __global__ __launch_bounds__(1024) void k_locate(EvalTable t, const float* __res
                                                  int32_t* __restrict__ seg, int64_t n, int flags) {
   extern __shared__ float4 lds_f4[];
   const Smem s = carve(lds_f4, t.N, t.K, false);
-  stage_table(t, nullptr, s);
-  __syncthreads();
-  if (flags & 2) {   // PWL_LOCATE_SEARCH
+  stage_table(t, nullptr, blockDim.x, s);
+  staged();
+  lds_barrier();
+  if (flags & kSearch) {
     locate_all<-1>(t, s, x, seg, n);
     return;
   }
@@ -175,11 +190,10 @@ __global__ void k_fill_zero(float* __restrict__ p, int64_t n) {
     p[i] = 0.0f;
 }
 
-// The vector path needs every point array at the same 16-byte phase (a
-// slice of aligned arrays qualifies); the head and tail points are scalar.
-inline bool same_phase(const void* a, const void* b) {
-  return b == nullptr || ((reinterpret_cast<uintptr_t>(a) ^ reinterpret_cast<uintptr_t>(b)) & 15u) == 0;
-}
+// The vector path takes arrays at any 4-byte alignment: its vectors sit on
+// the 16-byte boundaries of an array that is written, and the hardware reads
+// (and writes the other one) across those of the rest.
+inline bool word_aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
 
 // Launch shape of a streaming evaluation kernel: workgroups of `block`
 // threads, each thread handling `unroll` float4 vectors per iteration, on a
@@ -257,28 +271,32 @@ int get_records() { return g_records; }
 
 hipError_t launch_eval(const EvalTable& t, const float* vo, const float* x, float* y, int64_t n,
                        int num_cu, hipStream_t s) {
-  const bool vec = same_phase(x, y) && (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
+  const bool vec = word_aligned(x) && word_aligned(y);
   const LaunchConfig c = g_launch[0];
   const int rec = g_records;
   const size_t lds = rec == PWL_RECORDS_SOA     ? eval_lds_bytes_soa(t.N, t.K)
                      : rec == PWL_RECORDS_PAIRS ? eval_lds_bytes_pairs(t.N, t.K)
                                                 : eval_lds_bytes(t.N, t.K, false);
   const LaunchShape ls = stream_shape(c, lds, vec ? n / 4 : 0, n, num_cu);
-  const int v = (vec ? 1 : 0) | (g_locate == PWL_LOCATE_SEARCH ? 2 : 0);
-#define PWL_FWD(UU, RR) \
-  hipLaunchKernelGGL((k_eval_fwd<UU, RR>), dim3(ls.grid), dim3(ls.block), ls.lds, s, t, vo, x, y, n, v)
-#define PWL_FWD_U(RR)                   \
-  switch (c.unroll) {                   \
-    case 1: PWL_FWD(1, RR); break;      \
-    case 2: PWL_FWD(2, RR); break;      \
-    default: PWL_FWD(4, RR); break;     \
+  const int v = (vec ? kVec : 0) | (g_locate == PWL_LOCATE_SEARCH ? kSearch : 0) | (ls.block << kBlockBit);
+#define PWL_FWD(UU, RR, OO) \
+  hipLaunchKernelGGL((k_eval_fwd<UU, RR, OO>), dim3(ls.grid), dim3(ls.block), ls.lds, s, t, vo, x, y, n, v)
+#define PWL_FWD_U(RR, OO)                   \
+  switch (c.unroll) {                       \
+    case 1: PWL_FWD(1, RR, OO); break;      \
+    case 2: PWL_FWD(2, RR, OO); break;      \
+    default: PWL_FWD(4, RR, OO); break;     \
   }
   if (rec == PWL_RECORDS_SOA) {
-    PWL_FWD_U(PWL_RECORDS_SOA)
+    if (std::max({t.N, image_knot_words(t.N), image_map_words(t.K)}) <= ls.block) {
+      PWL_FWD_U(PWL_RECORDS_SOA, true)
+    } else {
+      PWL_FWD_U(PWL_RECORDS_SOA, false)
+    }
   } else if (rec == PWL_RECORDS_PAIRS) {
-    PWL_FWD_U(PWL_RECORDS_PAIRS)
+    PWL_FWD_U(PWL_RECORDS_PAIRS, false)
   } else {
-    PWL_FWD_U(PWL_RECORDS_PACKED)
+    PWL_FWD_U(PWL_RECORDS_PACKED, false)
   }
 #undef PWL_FWD_U
 #undef PWL_FWD
@@ -308,8 +326,7 @@ void launch_bwd_u(const LaunchShape& ls, int key, const EvalTable& t, const floa
 
 LaunchShape backward_shape(const EvalTable& t, const float* x, const float* g, const float* y, const float* dx,
                            bool wdv, int64_t n, int num_cu) {
-  const bool vec = same_phase(x, g) && same_phase(x, y) && same_phase(x, dx) &&
-                   (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
+  const bool vec = word_aligned(x) && word_aligned(g) && word_aligned(y) && word_aligned(dx);
   return stream_shape(g_launch[1], eval_lds_bytes(t.N, t.K, wdv), vec ? n / 4 : 0, n, num_cu);
 }
 
@@ -322,8 +339,7 @@ size_t backward_workspace_floats(const EvalTable& t, const float* x, const float
 hipError_t launch_eval_backward(const EvalTable& t, const float* vo, const float* x, const float* g,
                                 float* y, float* dx, float* dv, float* part, int64_t n, int num_cu,
                                 hipStream_t s) {
-  const bool vec = same_phase(x, g) && same_phase(x, y) && same_phase(x, dx) &&
-                   (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
+  const bool vec = word_aligned(x) && word_aligned(g) && word_aligned(y) && word_aligned(dx);
   const bool wdv = dv != nullptr;
   const LaunchConfig c = g_launch[1];
   const LaunchShape ls = backward_shape(t, x, g, y, dx, wdv, n, num_cu);
@@ -334,7 +350,7 @@ hipError_t launch_eval_backward(const EvalTable& t, const float* vo, const float
     return hipGetLastError();
   }
   if (wdv && part == nullptr) return hipErrorInvalidValue;
-  const int v = vec ? 1 : 0;
+  const int v = (vec ? kVec : 0) | (ls.block << kBlockBit);
   switch (c.unroll) {
     case 1: launch_bwd_u<1>(ls, key, t, vo, x, g, y, dx, part, n, v, s); break;
     case 2: launch_bwd_u<2>(ls, key, t, vo, x, g, y, dx, part, n, v, s); break;
@@ -352,7 +368,7 @@ hipError_t launch_eval_backward(const EvalTable& t, const float* vo, const float
 hipError_t launch_locate(const EvalTable& t, const float* x, int32_t* seg, int64_t n, int num_cu,
                          hipStream_t s) {
   const LaunchShape ls = stream_shape(g_launch[0], eval_lds_bytes(t.N, t.K, false), 0, n, num_cu);
-  const int v = (g_locate == PWL_LOCATE_SEARCH) ? 2 : 0;
+  const int v = (g_locate == PWL_LOCATE_SEARCH) ? kSearch : 0;
   hipLaunchKernelGGL(k_locate, dim3(ls.grid), dim3(ls.block), ls.lds, s, t, x, seg, n, v);
   return hipGetLastError();
 }
@@ -364,13 +380,14 @@ hipError_t configure_eval_kernels(int max_lds) {
   e = hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, lim);    \
   if (e != hipSuccess) return e;
   PWL_ATTR(k_locate)
-#define PWL_ATTR_R(RR)                   \
-  PWL_ATTR((k_eval_fwd<1, RR>))          \
-  PWL_ATTR((k_eval_fwd<2, RR>))          \
-  PWL_ATTR((k_eval_fwd<4, RR>))
-  PWL_ATTR_R(PWL_RECORDS_PACKED)
-  PWL_ATTR_R(PWL_RECORDS_SOA)
-  PWL_ATTR_R(PWL_RECORDS_PAIRS)
+#define PWL_ATTR_R(RR, OO)                   \
+  PWL_ATTR((k_eval_fwd<1, RR, OO>))          \
+  PWL_ATTR((k_eval_fwd<2, RR, OO>))          \
+  PWL_ATTR((k_eval_fwd<4, RR, OO>))
+  PWL_ATTR_R(PWL_RECORDS_PACKED, false)
+  PWL_ATTR_R(PWL_RECORDS_SOA, false)
+  PWL_ATTR_R(PWL_RECORDS_SOA, true)
+  PWL_ATTR_R(PWL_RECORDS_PAIRS, false)
 #undef PWL_ATTR_R
 #define PWL_ATTR_U(U)                            \
   PWL_ATTR((k_eval_bwd<U, false, false, true>))  \

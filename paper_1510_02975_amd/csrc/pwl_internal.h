@@ -31,11 +31,16 @@ struct FuncDesc {
   double s_a, s_h;
 };
 
-// Device view of a table's persistent arrays.
+// Device view of a table's persistent arrays.  The image a kernel copies to
+// LDS lies in memory as it stands there, padding included: rec, kimg and lo
+// back to back (image_words), and for the structure-of-arrays image soa,
+// with copies of kimg and lo behind its two fields (image_words_soa).
 struct TableDev {
   float4* rec;        // [N]   {x_k, v_k, slope_k, x_{k+1}}
+  float* kimg;        // [4 image_knot_words(N)] a, the interior knots, NaN from N on
+  uint16_t* lo;       // [8 image_map_words(K)] uniform index map: lo[u] = #{interior knots in cells < u}, u <= K
+  float* soa;         // the N values v_k, the N slopes, kimg, lo, each from a 16-byte word on
   float* knots;       // [N+1] FP32 knots
-  uint16_t* lo;       // [K+1] uniform index map: lo[u] = #{interior knots in cells < u}
   float* values;      // [N+1] FP32 vertex values
   double* knots64;    // [N+1] FP64 knots before rounding
   double* values64;   // [N+1] FP64 vertex values
@@ -44,14 +49,19 @@ struct TableDev {
   double* totals;     // [G] per-workgroup density sums
 };
 
-// Everything an evaluation kernel needs about a table.
-struct EvalTable {
-  const float4* rec;
-  const float* knots;
-  const uint16_t* lo;        // [K+1] uniform index map
-  const uint32_t* meta;      // [0] build flags, [1] most knots sharing one map cell
+// A table's shape: what the locate and the lerp need beside its arrays.
+struct TableShape {
   int32_t N, K;
   float a32, b32, scale32;   // cell(x) = floor((x - a32) * scale32), clamped to [0, K-1]
+};
+
+// Everything an evaluation kernel needs about a table.
+struct EvalTable : TableShape {
+  const float4* rec;         // the table's image: records, knots, map (TableDev)
+  const float* knots;        // [4 image_knot_words(N)] a, the interior knots, NaN from N on
+  const uint16_t* lo;        // [K+1] uniform index map
+  const float* soa;          // the structure-of-arrays image
+  const uint32_t* meta;      // [0] build flags, [1] most knots sharing one map cell
 };
 
 // Gauss-Legendre rule on [0, 1].
@@ -69,17 +79,19 @@ struct BuildParams {
   GaussRule gl;
 };
 
-// The LDS image of a table, in 16-byte words, each section starting on a
-// word: the N records, the knots with their NaN sentinels (N + kKnotPad
-// floats) and the u16 map lo[0..K], the last two rounded up to whole words.
+// The image of a table, in 16-byte words, each section starting on a word:
+// the N records, the knots with their NaN sentinels (a, x_1 .. x_{N-1}, then
+// NaN: N + kKnotPad floats) and the u16 map lo[0..K], the last two rounded
+// up to whole words.
 __host__ __device__ inline int image_knot_words(int N) { return (N + kKnotPad + 3) / 4; }
 __host__ __device__ inline int image_map_words(int K) { return (K + 1 + 7) / 8; }
 __host__ __device__ inline int image_words(int N, int K) { return N + image_knot_words(N) + image_map_words(K); }
-// The structure-of-arrays variant (forward only): each of the four record
-// fields is an array of N floats rounded up to whole words.
+// The structure-of-arrays variant (forward only): instead of the records the
+// values and the slopes, each N floats rounded up to whole words; x_k is
+// read from the knots (at N = 4096 80 KB against 112).
 __host__ __device__ inline int image_soa_field_words(int N) { return (N + 3) / 4; }
 __host__ __device__ inline int image_words_soa(int N, int K) {
-  return 4 * image_soa_field_words(N) + image_knot_words(N) + image_map_words(K);
+  return 2 * image_soa_field_words(N) + image_knot_words(N) + image_map_words(K);
 }
 
 // Copies of a workgroup's FP64 dL/dv in LDS (backward kernels): lane l adds

@@ -13,44 +13,41 @@ namespace pwl {
 namespace stream {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+// The same read from any 4-byte boundary (one 16-byte load either way).
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0), the other counters not waited for
 
 // Packed records: one 16-byte word per segment (a segment's lookup is one
 // LDS read of 12 or 16 bytes).
 struct Smem {
+  static constexpr bool kRecords = true;   // looked up by record(segment)
   float4* rec;      // [N]           {x_k, v_k, slope_k, x_{k+1}}
-  float* knot;      // [N + pad]     knot[k] = x_k for 1 <= k <= N-1, NaN elsewhere
+  float* knot;      // [N + pad]     knot[0] = a, knot[k] = x_k for 1 <= k <= N-1, NaN from N on
   uint16_t* lo;     // [K + 1]       lo[u] = #{interior knots in cells < u}; lo[K] = N - 1
   double* dv;       // [(N + 1) dvc] backward only: this workgroup's dL/dv, entry k of copy c at k dvc + c
   int dvc;          //               copies of dL/dv (a power of two; lane l adds into copy l mod dvc)
   __device__ __forceinline__ float4 record(int k) const { return rec[k]; }
-  __device__ __forceinline__ void put_record(int k, float4 r) const { rec[k] = r; }
 };
 
-// Structure-of-arrays records: the four fields of the records in four
-// arrays of N floats (a lookup reads each field it uses separately; the
-// forward's three reads are 4 bytes each).  Forward evaluation only.
+// Structure-of-arrays records: v_k and slope_k in arrays of N floats, x_k in
+// the knot array (no compare reads its entry 0).  A lookup reads the three fields separately, 4 bytes each.  Forward
+// evaluation only.
 struct SmemSoA {
-  float* rx;        // [N] x_k
+  static constexpr bool kRecords = true;
+  float* knot;      // [N + pad]  knot[0] = a, knot[k] = x_k for 1 <= k <= N-1, NaN from N on
   float* rv;        // [N] v_k
   float* rs;        // [N] slope_k
-  float* rw;        // [N] x_{k+1}
-  float* knot;
   uint16_t* lo;
-  __device__ __forceinline__ float4 record(int k) const { return make_float4(rx[k], rv[k], rs[k], rw[k]); }
-  __device__ __forceinline__ void put_record(int k, float4 r) const {
-    rx[k] = r.x;
-    rv[k] = r.y;
-    rs[k] = r.z;
-    rw[k] = r.w;
-  }
+  __device__ __forceinline__ float4 record(int k) const { return make_float4(knot[k], rv[k], rs[k], 0.0f); }
 };
 
 // Value/slope pairs: one 8-byte pair {v_k, slope_k} per segment, with x_k
-// read from the knot array, whose entry 0 holds a (no compare reads entry 0,
-// so it can): a point reads its map cell, the knots of its cell with the one
-// before them (the segment's own knot among them; adjacent, so one paired
+// read from the knot array: a point reads its map cell, the knots of its cell
+// with the one before them (the segment's own knot among them; adjacent, so one paired
 // read for a cell of one knot) and one pair.  Forward evaluation only.
 struct SmemPairs {
+  static constexpr bool kRecords = false;
   float2* vs;       // [N]        {v_k, slope_k}
   float* knot;      // [N + pad]  knot[0] = a, knot[k] = x_k for 1 <= k <= N-1, NaN from N on
   uint16_t* lo;
@@ -70,37 +67,31 @@ __device__ __forceinline__ Smem carve(void* base, int N, int K, bool backward) {
   return s;
 }
 
-// The structure-of-arrays image: four record arrays of image_soa_field_words
-// words each, then the knots and the map as in carve.
-__device__ __forceinline__ SmemSoA carve_soa(void* base, int N, int K) {
+// The structure-of-arrays image: values, slopes, knots, map.
+__device__ __forceinline__ SmemSoA carve_soa(void* base, int N) {
   SmemSoA s;
   const int fw = image_soa_field_words(N);
   float4* b4 = reinterpret_cast<float4*>(base);
-  s.rx = reinterpret_cast<float*>(b4);
-  s.rv = reinterpret_cast<float*>(b4 + fw);
-  s.rs = reinterpret_cast<float*>(b4 + 2 * fw);
-  s.rw = reinterpret_cast<float*>(b4 + 3 * fw);
-  s.knot = reinterpret_cast<float*>(b4 + 4 * fw);
-  s.lo = reinterpret_cast<uint16_t*>(reinterpret_cast<float4*>(s.knot) + image_knot_words(N));
-  (void)K;
+  s.rv = reinterpret_cast<float*>(b4);
+  s.rs = reinterpret_cast<float*>(b4 + fw);
+  s.knot = reinterpret_cast<float*>(b4 + 2 * fw);
+  s.lo = reinterpret_cast<uint16_t*>(b4 + 2 * fw + image_knot_words(N));
   return s;
 }
 
 // The pairs image: the pairs (two per 16-byte word), then the knots and the
 // map as in carve.
-__device__ __forceinline__ SmemPairs carve_pairs(void* base, int N, int K) {
+__device__ __forceinline__ SmemPairs carve_pairs(void* base, int N) {
   SmemPairs s;
   float4* b4 = reinterpret_cast<float4*>(base);
   s.vs = reinterpret_cast<float2*>(b4);
   s.knot = reinterpret_cast<float*>(b4 + image_pair_words(N));
   s.lo = reinterpret_cast<uint16_t*>(reinterpret_cast<float4*>(s.knot) + image_knot_words(N));
-  (void)K;
   return s;
 }
 
-// The words of the table's image (see image_words; the table's arrays are
-// 256-byte aligned).  A record, with v_override its value and slope
-// re-derived as (v_{k+1} - v_k) / (x_{k+1} - x_k) in FP32:
+// Record w, with v_override its value and slope re-derived as
+// (v_{k+1} - v_k) / (x_{k+1} - x_k) in FP32.
 __device__ __forceinline__ float4 record_word(const EvalTable& t, const float* __restrict__ vo, int w) {
   float4 r = t.rec[w];
   if (vo != nullptr) {
@@ -111,71 +102,107 @@ __device__ __forceinline__ float4 record_word(const EvalTable& t, const float* _
   return r;
 }
 
-// knots 4w .. 4w+3, NaN outside the interior knots 1..N-1 (so that every
-// compare against a sentinel is false, even for x = +inf):
-__device__ __forceinline__ float4 knot_word(const EvalTable& t, int w) {
-  const int k0 = 4 * w;
-  if (k0 >= 1 && k0 + 3 <= t.N - 1) return *reinterpret_cast<const float4*>(t.knots + k0);
-  float e[4];
+// Staging.  nt is the workgroup's size, passed as an argument (blockDim is a
+// memory load at the head of every kernel that reads it).
+
+// Words 0 .. n-1, word(w) put to LDS by put(w, .), four per thread per
+// round: a round's loads are all issued before its first write (indices
+// clamped: a load under a per-thread condition would be waited for before
+// the next).
+template <class Word, class Put>
+__device__ __forceinline__ void stage_rounds(int n, int nt, const Word& word, const Put& put) {
+  const int tid = threadIdx.x;
+  for (int k0 = 0; k0 < n; k0 += 4 * nt) {
+    float4 w[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int k = k0 + i;
-    e[i] = (k >= 1 && k <= t.N - 1) ? t.knots[k] : __builtin_nanf("");
-  }
-  return make_float4(e[0], e[1], e[2], e[3]);
-}
-
-// The same with entry 0 = a (the pairs image):
-__device__ __forceinline__ float4 knot_word_a(const EvalTable& t, int w) {
-  float4 k = knot_word(t, w);
-  if (w == 0) k.x = t.a32;
-  return k;
-}
-
-// map entries 8w .. 8w+7, 0 past lo[K]:
-__device__ __forceinline__ float4 map_word(const EvalTable& t, int w) {
-  const int u0 = 8 * w;
-  if (u0 + 7 <= t.K) return *reinterpret_cast<const float4*>(t.lo + u0);
-  uint32_t p[4];
+    for (int j = 0; j < 4; ++j) w[j] = word(min(k0 + j * nt + tid, n - 1));
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int u = u0 + 2 * i;
-    const uint32_t lo = (u <= t.K) ? t.lo[u] : 0u, hi = (u + 1 <= t.K) ? t.lo[u + 1] : 0u;
-    p[i] = lo | (hi << 16);
+    for (int j = 0; j < 4; ++j)
+      if (k0 + j * nt + tid < n) put(k0 + j * nt + tid, w[j]);
   }
-  return make_float4(__uint_as_float(p[0]), __uint_as_float(p[1]), __uint_as_float(p[2]), __uint_as_float(p[3]));
 }
 
-// Copy the table's image to `s` (LDS, or a batch's image in global memory).
-// When every section fits in one word per thread (N no larger than the
-// workgroup), each thread loads its words before it writes any, so the copy
-// waits on one round of loads instead of one per section; the straight-line
-// form keeps the kernels' register use where the streaming loop needs it.
-template <class S>
-__device__ __forceinline__ void stage_table(const EvalTable& t, const float* __restrict__ vo, const S& s) {
-  const int tid = threadIdx.x, nt = blockDim.x;
+__device__ __forceinline__ int wave_first() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63; }
+
+// Copies n words from global memory to LDS without a register in between:
+// all of a wave's loads are in flight at once (lane l's word lands at its
+// wave's base + l).  The copy has arrived after staged().
+__device__ __forceinline__ void stage_copy(const void* __restrict__ src, int n, int nt, void* dst) {
+  const float4* __restrict__ s4 = reinterpret_cast<const float4*>(src);
+  float4* d4 = reinterpret_cast<float4*>(dst);
+  const int lane = threadIdx.x & 63;
+  for (int w0 = wave_first(); w0 < n; w0 += nt) {
+    if (w0 + lane < n)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s4 + w0 + lane),
+                                       (__attribute__((address_space(3))) void*)(d4 + w0), 16, 0, 0);
+  }
+}
+
+// The structure-of-arrays image when each of its sections fits in one word
+// per thread: every thread loads its words before it writes any.
+__device__ __forceinline__ void stage_once(const EvalTable& t, const float* __restrict__ vo, const SmemSoA& s) {
+  const int tid = threadIdx.x;
   const int nkw = image_knot_words(t.N), nmw = image_map_words(t.K);
   float4* knot4 = reinterpret_cast<float4*>(s.knot);
   float4* map4 = reinterpret_cast<float4*>(s.lo);
-  if (t.N <= nt && nkw <= nt && nmw <= nt) {
-    const bool hr = tid < t.N, hk = tid < nkw, hm = tid < nmw;
-    float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f), k = r, m = r;
-    if (hr) r = record_word(t, vo, tid);
-    if (hk) k = knot_word(t, tid);
-    if (hm) m = map_word(t, tid);
-    if (hr) s.put_record(tid, r);
-    if (hk) knot4[tid] = k;
-    if (hm) map4[tid] = m;
-    return;
+  const bool hr = tid < t.N, hk = tid < nkw, hm = tid < nmw;
+  float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f), k = r, m = r;
+  if (hr) r = record_word(t, vo, tid);
+  if (hk) k = reinterpret_cast<const float4*>(t.knots)[tid];
+  if (hm) m = reinterpret_cast<const float4*>(t.lo)[tid];
+  if (hr) {
+    s.rv[tid] = r.y;
+    s.rs[tid] = r.z;
   }
-  for (int w = tid; w < t.N; w += nt) s.put_record(w, record_word(t, vo, w));
-  for (int w = tid; w < nkw; w += nt) knot4[w] = knot_word(t, w);
-  for (int w = tid; w < nmw; w += nt) map4[w] = map_word(t, w);
+  if (hk) knot4[tid] = k;
+  if (hm) map4[tid] = m;
+}
+
+// Waits for the wave's own part of the staging (and its other loads in
+// flight); a barrier then makes the whole image visible.
+__device__ __forceinline__ void staged() { __builtin_amdgcn_s_waitcnt(kWaitVm0); }
+
+// Copies the table's image to LDS; with v_override the values and slopes are
+// re-derived on the way.  staged() ends the copy.  (The override's path ends
+// its own loads: pending ones would make the compiler wait for the copy
+// where the paths join.)
+__device__ __forceinline__ void stage_table(const EvalTable& t, const float* __restrict__ vo, int nt, const Smem& s) {
+  const int nkm = image_knot_words(t.N) + image_map_words(t.K);
+  if (vo == nullptr) {
+    stage_copy(t.rec, t.N + nkm, nt, s.rec);
+  } else {
+    stage_copy(t.knots, nkm, nt, s.knot);
+    stage_rounds(t.N, nt, [&](int w) { return record_word(t, vo, w); }, [&](int w, float4 r) { s.rec[w] = r; });
+    staged();
+  }
+}
+
+__device__ __forceinline__ void stage_table(const EvalTable& t, const float* __restrict__ vo, int nt,
+                                            const SmemSoA& s) {
+  const int fw = image_soa_field_words(t.N), nkm = image_knot_words(t.N) + image_map_words(t.K);
+  if (vo == nullptr) {
+    stage_copy(t.soa, 2 * fw + nkm, nt, s.rv);
+  } else {
+    stage_copy(t.soa + 8 * fw, nkm, nt, s.knot);
+    stage_rounds(t.N, nt, [&](int w) { return record_word(t, vo, w); }, [&](int w, float4 r) {
+      s.rv[w] = r.y;
+      s.rs[w] = r.z;
+    });
+    staged();
+  }
+}
+
+// A workgroup barrier that orders LDS accesses only: global loads and
+// stores a wave still has in flight are not waited for (__syncthreads
+// would).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // The pairs image: word w holds the pairs of segments 2w and 2w + 1 (zero
-// past N - 1); sections as in stage_table, each in one round of loads when
-// it fits in one word per thread.
+// past N - 1).
 __device__ __forceinline__ float4 pair_word(const EvalTable& t, const float* __restrict__ vo, int w) {
   const float4 r0 = record_word(t, vo, 2 * w);
   float4 r1 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -183,27 +210,13 @@ __device__ __forceinline__ float4 pair_word(const EvalTable& t, const float* __r
   return make_float4(r0.y, r0.z, r1.y, r1.z);
 }
 
-__device__ __forceinline__ void stage_table_pairs(const EvalTable& t, const float* __restrict__ vo,
-                                                  const SmemPairs& s) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int npw = image_pair_words(t.N), nkw = image_knot_words(t.N), nmw = image_map_words(t.K);
+__device__ __forceinline__ void stage_table(const EvalTable& t, const float* __restrict__ vo, int nt,
+                                            const SmemPairs& s) {
+  stage_copy(t.knots, image_knot_words(t.N) + image_map_words(t.K), nt, s.knot);
   float4* pair4 = reinterpret_cast<float4*>(s.vs);
-  float4* knot4 = reinterpret_cast<float4*>(s.knot);
-  float4* map4 = reinterpret_cast<float4*>(s.lo);
-  if (npw <= nt && nkw <= nt && nmw <= nt) {
-    const bool hp = tid < npw, hk = tid < nkw, hm = tid < nmw;
-    float4 p = make_float4(0.0f, 0.0f, 0.0f, 0.0f), k = p, m = p;
-    if (hp) p = pair_word(t, vo, tid);
-    if (hk) k = knot_word_a(t, tid);
-    if (hm) m = map_word(t, tid);
-    if (hp) pair4[tid] = p;
-    if (hk) knot4[tid] = k;
-    if (hm) map4[tid] = m;
-    return;
-  }
-  for (int w = tid; w < npw; w += nt) pair4[w] = pair_word(t, vo, w);
-  for (int w = tid; w < nkw; w += nt) knot4[w] = knot_word_a(t, w);
-  for (int w = tid; w < nmw; w += nt) map4[w] = map_word(t, w);
+  stage_rounds(image_pair_words(t.N), nt, [&](int w) { return pair_word(t, vo, w); },
+               [&](int w, float4 p) { pair4[w] = p; });
+  staged();
 }
 
 __device__ __forceinline__ float clamp_nan(float x, float a, float b) {
@@ -215,7 +228,7 @@ __device__ __forceinline__ float clamp_nan(float x, float a, float b) {
 // greater than x (they lie in later cells) and the sentinels are NaN, so the
 // extra compares are false; the count of true compares is exact.
 template <int MAXC, class S>
-__device__ __forceinline__ int locate_fixed(float x, const EvalTable& t, const S& s) {
+__device__ __forceinline__ int locate_fixed(float x, const TableShape& t, const S& s) {
   const int u = map_cell(x, t.a32, t.scale32, t.K);
   const int lo = s.lo[u];
   int seg = lo;
@@ -226,7 +239,7 @@ __device__ __forceinline__ int locate_fixed(float x, const EvalTable& t, const S
 
 // Any number of knots per cell: the count is lo[u+1] - lo[u].
 template <class S>
-__device__ __forceinline__ int locate_any(float x, const EvalTable& t, const S& s) {
+__device__ __forceinline__ int locate_any(float x, const TableShape& t, const S& s) {
   const int u = map_cell(x, t.a32, t.scale32, t.K);
   const int lo = s.lo[u];
   const int cnt = (int)s.lo[u + 1] - lo;
@@ -240,7 +253,7 @@ __device__ __forceinline__ int locate_any(float x, const EvalTable& t, const S& 
 // (so x_i <= x < x_{i+1}; NaN x compares false and gives 0), halving a
 // power-of-two step from the largest one below N.
 template <class S>
-__device__ __forceinline__ int locate_search(float x, const EvalTable& t, const S& s) {
+__device__ __forceinline__ int locate_search(float x, const TableShape& t, const S& s) {
   int lo = 0;
   for (int half = (t.N > 1) ? (1 << (31 - __builtin_clz(t.N - 1))) : 0; half >= 1; half >>= 1) {
     const int k = lo + half;
@@ -252,14 +265,14 @@ __device__ __forceinline__ int locate_search(float x, const EvalTable& t, const 
 // MAXC > 0: map + MAXC unrolled compares; 0: map + counted compares;
 // -1: binary search without the map.
 template <int MAXC, class S>
-__device__ __forceinline__ int locate(float x, const EvalTable& t, const S& s) {
+__device__ __forceinline__ int locate(float x, const TableShape& t, const S& s) {
   if (MAXC > 0) return locate_fixed<MAXC>(x, t, s);
   if (MAXC < 0) return locate_search(x, t, s);
   return locate_any(x, t, s);
 }
 
 template <int MAXC, class S>
-__device__ __forceinline__ float eval_point(float x, const EvalTable& t, const S& s) {
+__device__ __forceinline__ float eval_point(float x, const TableShape& t, const S& s) {
   const int seg = locate<MAXC>(x, t, s);
   const float4 r = s.record(seg);
   return fmaf(clamp_nan(x, t.a32, t.b32) - r.x, r.z, r.y);
@@ -271,7 +284,7 @@ __device__ __forceinline__ float eval_point(float x, const EvalTable& t, const S
 // adjacent; otherwise it is read after the locate.  The same operations on
 // the same values as eval_point, so the outputs are bit-identical.
 template <int MAXC>
-__device__ __forceinline__ float eval_point(float x, const EvalTable& t, const SmemPairs& s) {
+__device__ __forceinline__ float eval_point(float x, const TableShape& t, const SmemPairs& s) {
   int seg;
   float xs;
   if (MAXC > 0) {
@@ -295,7 +308,7 @@ __device__ __forceinline__ float eval_point(float x, const EvalTable& t, const S
 }
 
 template <int MAXC, bool WY, bool WDX, bool WDV>
-__device__ __forceinline__ void backward_point(float x, float g, const EvalTable& t, const Smem& s,
+__device__ __forceinline__ void backward_point(float x, float g, const TableShape& t, const Smem& s,
                                                float& y, float& dx) {
   const int seg = locate<MAXC>(x, t, s);
   const float4 r = s.rec[seg];
@@ -325,38 +338,13 @@ __device__ __forceinline__ void backward_point(float x, float g, const EvalTable
   }
 }
 
-// One iteration over U float4 vectors per thread: all loads, then all table
-// lookups, then all stores.  Full iterations run unguarded so the compiler
-// can count outstanding memory operations exactly (a guarded load makes
-// every later wait a wait for all stores); the last, partial iteration of a
-// thread is guarded.
-template <int U, int MAXC, bool GUARD, class S>
-__device__ __forceinline__ void fwd_iter(const EvalTable& t, const S& s, const v4f* __restrict__ x4,
-                                         v4f* __restrict__ y4, int64_t base, int64_t bs, int64_t n4) {
-  v4f xv[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int64_t i = base + u * bs;
-    if (!GUARD || i < n4) xv[u] = __builtin_nontemporal_load(x4 + i);
-  }
-  v4f yv[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    yv[u].x = eval_point<MAXC>(xv[u].x, t, s);
-    yv[u].y = eval_point<MAXC>(xv[u].y, t, s);
-    yv[u].z = eval_point<MAXC>(xv[u].z, t, s);
-    yv[u].w = eval_point<MAXC>(xv[u].w, t, s);
-  }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int64_t i = base + u * bs;
-    if (!GUARD || i < n4) __builtin_nontemporal_store(yv[u], y4 + i);
-  }
-}
-
-// Which points of [begin, end) go through 16-byte vectors: the arrays share
-// their alignment phase (vec), so [head, 4 vend) is vectorised and the
-// points before `head` and from max(head, 4 vend) on are scalar.
+// Which points of [begin, end) go through 16-byte vectors on the 16-byte
+// boundaries of array p (the arrays are then 4-byte aligned: vec):
+// [head, 4 vend) is vectorised and the points before `head` and from
+// max(head, 4 vend) on are scalar.  p is an array that is written; the
+// others are read (a second output written) across their own boundaries,
+// which the hardware does for any 4-byte address.  2^23.6 points with x one
+// element off y's boundaries: 27.8 us point by point, 19.1 us so.
 struct Split {
   int64_t head, vbeg, vend;
 };
@@ -379,27 +367,62 @@ __device__ __forceinline__ Split split_range(const float* p, int64_t begin, int6
   return r;
 }
 
+// Lookups of one vector.
+template <int MAXC, class S>
+__device__ __forceinline__ v4f eval_vec(const v4f& xv, const TableShape& t, const S& s) {
+  v4f yv;
+  yv.x = eval_point<MAXC>(xv.x, t, s);
+  yv.y = eval_point<MAXC>(xv.y, t, s);
+  yv.z = eval_point<MAXC>(xv.z, t, s);
+  yv.w = eval_point<MAXC>(xv.w, t, s);
+  return yv;
+}
+
+// One iteration over U float4 vectors per thread: all loads, then all table
+// lookups, then all stores.  Full iterations run unguarded so the compiler
+// can count outstanding memory operations exactly (a guarded load makes
+// every later wait a wait for all stores); the last, partial iteration of a
+// thread is guarded.
+template <int U, int MAXC, bool GUARD, class S>
+__device__ __forceinline__ void fwd_iter(const TableShape& t, const S& s, const v4fu* __restrict__ x4,
+                                         v4f* __restrict__ y4, int64_t base, int64_t bs, int64_t n4) {
+  v4f xv[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t i = base + u * bs;
+    if (!GUARD || i < n4) xv[u] = __builtin_nontemporal_load(x4 + i);
+  }
+  v4f yv[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) yv[u] = eval_vec<MAXC>(xv[u], t, s);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t i = base + u * bs;
+    if (!GUARD || i < n4) __builtin_nontemporal_store(yv[u], y4 + i);
+  }
+}
+
 // Forward over points [begin, end) by `nblk` cooperating workgroups (this one
 // is number `blk`): workgroup blk streams vectors blk*bs*U + u*bs + tid of
 // each stride of nblk*bs*U vectors.
 template <int U, int MAXC, class S>
 __device__ __forceinline__ void fwd_range(const EvalTable& t, const S& s, const float* __restrict__ x,
                                           float* __restrict__ y, int64_t begin, int64_t end, bool vec,
-                                          int64_t blk, int64_t nblk) {
-  const Split sp = split_range(x, begin, end, vec);
-  const int64_t bs = blockDim.x, tid = threadIdx.x;
+                                          int64_t blk, int64_t nblk, int nt) {
+  const Split sp = split_range(y, begin, end, vec);
+  const int64_t bs = nt, tid = threadIdx.x;
   const int64_t gtid = blk * bs + tid, gthreads = nblk * bs;
   for (int64_t i = begin + gtid; i < sp.head; i += gthreads) y[i] = eval_point<MAXC>(x[i], t, s);
   if (sp.vend > sp.vbeg) {
-    const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(x) >> 2) & 3);
-    const v4f* __restrict__ x4 = reinterpret_cast<const v4f*>(x - phase);
+    const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(y) >> 2) & 3);
+    const v4fu* __restrict__ x4 = reinterpret_cast<const v4fu*>(x - phase);
     v4f* __restrict__ y4 = reinterpret_cast<v4f*>(y - phase);
     const int64_t stride = nblk * bs * U;
     int64_t base = sp.vbeg + blk * bs * U + tid;
     for (; base + (U - 1) * bs < sp.vend; base += stride) fwd_iter<U, MAXC, false>(t, s, x4, y4, base, bs, sp.vend);
     if (base < sp.vend) fwd_iter<U, MAXC, true>(t, s, x4, y4, base, bs, sp.vend);
   }
-  const int64_t tail = (sp.vend > sp.vbeg) ? 4 * sp.vend - (int64_t)((reinterpret_cast<uintptr_t>(x) >> 2) & 3)
+  const int64_t tail = (sp.vend > sp.vbeg) ? 4 * sp.vend - (int64_t)((reinterpret_cast<uintptr_t>(y) >> 2) & 3)
                                            : sp.head;
   for (int64_t i = (tail > sp.head ? tail : sp.head) + gtid; i < end; i += gthreads)
     y[i] = eval_point<MAXC>(x[i], t, s);
@@ -408,9 +431,9 @@ __device__ __forceinline__ void fwd_range(const EvalTable& t, const S& s, const 
 template <int U, bool WY, bool WDX, bool WDV>
 struct Bwd {
   template <int MAXC, bool GUARD>
-  __device__ __forceinline__ static void iter(const EvalTable& t, const Smem& s, const v4f* __restrict__ x4,
-                                              const v4f* __restrict__ g4, v4f* __restrict__ y4,
-                                              v4f* __restrict__ dx4, int64_t base, int64_t bs, int64_t n4) {
+  __device__ __forceinline__ static void iter(const TableShape& t, const Smem& s, const v4fu* __restrict__ x4,
+                                              const v4fu* __restrict__ g4, v4fu* __restrict__ y4,
+                                              v4fu* __restrict__ dx4, int64_t base, int64_t bs, int64_t n4) {
     v4f xv[U], gv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -434,8 +457,8 @@ struct Bwd {
     for (int u = 0; u < U; ++u) {
       const int64_t i = base + u * bs;
       if (!GUARD || i < n4) {
-        if (WY) __builtin_nontemporal_store(yv[u], y4 + i);
-        if (WDX) __builtin_nontemporal_store(dxv[u], dx4 + i);
+        if (WY) __builtin_nontemporal_store((v4fu)yv[u], y4 + i);
+        if (WDX) __builtin_nontemporal_store((v4fu)dxv[u], dx4 + i);
       }
     }
   }
@@ -443,20 +466,21 @@ struct Bwd {
   // Fused forward + backward over points [begin, end), cooperating
   // workgroups as in fwd_range.
   template <int MAXC>
-  __device__ __forceinline__ static void range(const EvalTable& t, const Smem& s,
+  __device__ __forceinline__ static void range(const TableShape& t, const Smem& s,
                                                const float* __restrict__ x, const float* __restrict__ g,
                                                float* __restrict__ y, float* __restrict__ dx, int64_t begin,
-                                               int64_t end, bool vec, int64_t blk, int64_t nblk) {
-    const Split sp = split_range(x, begin, end, vec);
-    const int64_t bs = blockDim.x, tid = threadIdx.x;
+                                               int64_t end, bool vec, int64_t blk, int64_t nblk, int nt) {
+    const float* aligned = WY ? y : (WDX ? dx : x);
+    const Split sp = split_range(aligned, begin, end, vec);
+    const int64_t bs = nt, tid = threadIdx.x;
     const int64_t gtid = blk * bs + tid, gthreads = nblk * bs;
     for (int64_t i = begin + gtid; i < sp.head; i += gthreads) scalar<MAXC>(t, s, x, g, y, dx, i);
-    const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(x) >> 2) & 3);
+    const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(aligned) >> 2) & 3);
     if (sp.vend > sp.vbeg) {
-      const v4f* __restrict__ x4 = reinterpret_cast<const v4f*>(x - phase);
-      const v4f* __restrict__ g4 = reinterpret_cast<const v4f*>(g - phase);
-      v4f* __restrict__ y4 = WY ? reinterpret_cast<v4f*>(y - phase) : nullptr;
-      v4f* __restrict__ dx4 = WDX ? reinterpret_cast<v4f*>(dx - phase) : nullptr;
+      const v4fu* __restrict__ x4 = reinterpret_cast<const v4fu*>(x - phase);
+      const v4fu* __restrict__ g4 = reinterpret_cast<const v4fu*>(g - phase);
+      v4fu* __restrict__ y4 = WY ? reinterpret_cast<v4fu*>(y - phase) : nullptr;
+      v4fu* __restrict__ dx4 = WDX ? reinterpret_cast<v4fu*>(dx - phase) : nullptr;
       const int64_t stride = nblk * bs * U;
       int64_t base = sp.vbeg + blk * bs * U + tid;
       for (; base + (U - 1) * bs < sp.vend; base += stride)
@@ -469,7 +493,7 @@ struct Bwd {
   }
 
   template <int MAXC>
-  __device__ __forceinline__ static void scalar(const EvalTable& t, const Smem& s, const float* __restrict__ x,
+  __device__ __forceinline__ static void scalar(const TableShape& t, const Smem& s, const float* __restrict__ x,
                                                 const float* __restrict__ g, float* __restrict__ y,
                                                 float* __restrict__ dx, int64_t i) {
     float yy = 0.0f, dd = 0.0f;
