@@ -413,8 +413,10 @@ pwl_status pwl_kde(const pwl_table* t, int32_t mode, const void* frame, const vo
  * batch's slices round-robin.
  * The single-table kernels cut the grid back, a whole workgroup per compute
  * unit at a time and to no fewer than one per compute unit, until each
- * workgroup streams at least 2^15 points and 2 points per byte of the table
- * it stages in LDS.  All three
+ * workgroup streams at least 2^15 points, and more for tables that take
+ * longer to stage.  A launch with fewer points than fill one workgroup of
+ * this shape per compute unit runs in smaller workgroups with fewer vectors
+ * per thread, so that it spreads over the compute units.  All three
  * zero restores the default.  Used by the autotuner; takes effect for later
  * launches.
  * pwl_get_launch reads the current shape back (outputs nullable).

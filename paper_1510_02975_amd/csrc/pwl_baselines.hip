@@ -134,7 +134,7 @@ LaunchShape baseline_shape(int64_t n4, int64_t n, int num_cu) {
   const int64_t work = (n4 > 0) ? (n4 + block * kStreamUnroll - 1) / (block * kStreamUnroll)
                                 : (n + block - 1) / block;
   const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)num_cu * 8, work));
-  return LaunchShape{block, grid, 0};
+  return LaunchShape{block, grid, 0, kStreamUnroll};
 }
 
 }  // namespace

@@ -25,7 +25,8 @@ namespace {
 constexpr size_t kLdsPerCU = 160 * 1024;
 constexpr int kXcds = 8;             // MI355X accelerator complex dies; workgroups go to them round-robin
 constexpr int64_t kMinPointsPerWG = int64_t(1) << 15;   // streaming grids: points per workgroup, at least
-constexpr int64_t kPointsPerStagedByte = 2;             // and per byte of table the workgroup stages
+constexpr int64_t kMaxPointsPerWG = 57344;              // (forward) no more asked for by the staged bytes
+constexpr int64_t kPointsPerStagedByte = 2;             // (backward) and per byte of table the workgroup stages
 
 using namespace stream;
 
@@ -203,36 +204,79 @@ inline bool word_aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p)
 // and XCDs that stream faster take more of the points, where a grid of one
 // resident round waits for its slowest CU.  Each workgroup stages the whole
 // table, so the grid is cut back, a whole workgroup per CU at a time (a
-// partial last round leaves CUs idle), until a workgroup streams at least
-// kMinPointsPerWG points and at least kPointsPerStagedByte points per byte
-// of table it stages, but never below one workgroup per CU (nor above one
-// per iteration of work).  The defaults are the autotuner's choice on
-// MI355X: forward at 2^28 points, four vectors per thread in 1024-thread
-// workgroups, up to 32 per CU (at N = 1024 the staging rule leaves 18,
-// which measured 333 us against 335 us for 16; at N = 4096 it leaves about
-// 3); fused backward at 2^26 points,
-// two vectors per thread (the dL/dv LDS atomics favour a smaller register
-// footprint) in one 768-thread workgroup per CU - every further workgroup
-// there adds a dL/dv flush and a column to reduce.  The batched kernels
-// take 1024-thread workgroups and four vectors per thread: the forward a
-// persistent grid of 3 per CU, the fused backward 32 per CU (about one
-// slice per workgroup, in rounds; its four-vector body spills a little and
-// still measured 3% faster than two vectors in 3 per CU).  pwl_set_launch
-// overrides them.
+// partial last round leaves CUs idle), until a workgroup streams enough
+// points, but never below one workgroup per CU (nor above one per iteration
+// of work).  The defaults are the autotuner's choice on MI355X: forward at
+// 2^28 points, four vectors per thread in 1024-thread workgroups, up to 32
+// per CU; fused backward at 2^26 points, two vectors per thread (the dL/dv
+// LDS atomics favour a smaller register footprint) in one 768-thread
+// workgroup per CU - every further workgroup there adds a dL/dv flush and a
+// column to reduce.  The batched kernels take 1024-thread workgroups and
+// four vectors per thread: the forward a persistent grid of 3 per CU, the
+// fused backward 32 per CU (about one slice per workgroup, in rounds; its
+// four-vector body spills a little and still measured 3% faster than two
+// vectors in 3 per CU).  pwl_set_launch overrides them.
+//
+// Enough points, forward: 2^15, and 2.75 per byte of the image up to 57344.
+// At 2^28 points N = 16 takes 32 per CU (328 us; 18: 334) and N = 1024 and
+// 4096 take 18 (333 and 346 us; 25 per CU 335 and 352, 3 per CU 360); N = 4096
+// at 2^27 points 9 (177 us; 3: 181, 18: 185).
+//
+// A launch too small to give every CU a workgroup of the tuned shape spreads
+// over the CUs instead, in smaller workgroups with fewer vectors per thread.
+// Forward: one vector per thread up to 1024 per CU, two up to 2048; of 256,
+// 512 and 1024 threads the fewest whose workgroups stage at most 48 KB per
+// CU together (or are alone on it).  Kernel times in us, the tuned shape ->
+// this one: N = 64, 2^20 points 6.2 -> 3.9; N = 1024, 2^14 6.9 -> 3.1, 2^20
+// 7.5 -> 4.7 (256 threads 5.0); N = 4096, 2^20 8.0 -> 5.2 (512 threads 7.0).
+// Backward: one vector per thread in 256 threads (512 for N above 1024) up
+// to 512 vectors per CU, then two in 512 threads up to 1024: with the dL/dv
+// reduction N = 64, 2^17 points 8.5 -> 7.0; N = 4096, 2^17 12.6 -> 11.7.
 constexpr LaunchConfig kDefaultLaunch[4] = {{4, 1024, 32}, {2, 768, 1}, {4, 1024, 3}, {4, 1024, 32}};
 LaunchConfig g_launch[4] = {kDefaultLaunch[0], kDefaultLaunch[1], kDefaultLaunch[2], kDefaultLaunch[3]};
 int g_locate = PWL_LOCATE_MAP;
 int g_records = PWL_RECORDS_PACKED;
 
-LaunchShape stream_shape(const LaunchConfig& c, size_t lds, int64_t n4, int64_t n, int num_cu) {
+// The tuned shape on the grid it earns: at least min_points points per workgroup.
+LaunchShape stream_shape(const LaunchConfig& c, size_t lds, int64_t min_points, int64_t n4, int64_t n, int num_cu) {
   const int block = c.block;
   const int64_t per_wg = (int64_t)block * c.unroll;
   const int64_t work = (n4 > 0) ? (n4 + per_wg - 1) / per_wg : (n + block - 1) / block;
-  const int64_t min_points = std::max<int64_t>(kMinPointsPerWG, kPointsPerStagedByte * (int64_t)lds);
   // whole workgroups per CU: a last partial round would leave CUs idle
   const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(c.wg_per_cu, n / (min_points * num_cu)));
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>((int64_t)num_cu * per_cu, work));
-  return LaunchShape{block, (int)grid, lds};
+  return LaunchShape{block, (int)grid, lds, c.unroll};
+}
+
+// A small launch: `unroll` vectors per thread in workgroups of `block`
+// threads (at most the tuned ones'), as many as there is work for.
+LaunchShape small_shape(const LaunchConfig& c, int unroll, int block, size_t lds, int64_t n4, int num_cu) {
+  unroll = std::min(unroll, c.unroll);
+  block = std::min(block, c.block);
+  const int64_t per_wg = (int64_t)block * unroll;
+  const int64_t grid = std::min<int64_t>((int64_t)num_cu * c.wg_per_cu, (n4 + per_wg - 1) / per_wg);
+  return LaunchShape{block, (int)grid, lds, unroll};
+}
+
+bool is_small(const LaunchConfig& c, int64_t n4, int num_cu) {
+  return n4 > 0 && n4 < (int64_t)num_cu * c.block * c.unroll;
+}
+
+LaunchShape forward_shape(size_t lds, int64_t n4, int64_t n, int num_cu) {
+  const LaunchConfig c = g_launch[PWL_KERNEL_FORWARD];
+  if (is_small(c, n4, num_cu)) {
+    const int64_t v = (n4 + num_cu - 1) / num_cu;   // vectors per CU
+    const int unroll = v <= 1024 ? 1 : (v <= 2048 ? 2 : 4);
+    int block = 256;
+    while (block < 1024) {
+      const int64_t wgs = (v + (int64_t)block * unroll - 1) / ((int64_t)block * unroll);
+      if (wgs == 1 || wgs * (int64_t)lds <= 48 * 1024) break;
+      block *= 2;
+    }
+    return small_shape(c, unroll, block, lds, n4, num_cu);
+  }
+  const int64_t staged = std::min<int64_t>(kMaxPointsPerWG, 11 * (int64_t)lds / 4);
+  return stream_shape(c, lds, std::max(kMinPointsPerWG, staged), n4, n, num_cu);
 }
 
 }  // namespace
@@ -272,17 +316,16 @@ int get_records() { return g_records; }
 hipError_t launch_eval(const EvalTable& t, const float* vo, const float* x, float* y, int64_t n,
                        int num_cu, hipStream_t s) {
   const bool vec = word_aligned(x) && word_aligned(y);
-  const LaunchConfig c = g_launch[0];
   const int rec = g_records;
   const size_t lds = rec == PWL_RECORDS_SOA     ? eval_lds_bytes_soa(t.N, t.K)
                      : rec == PWL_RECORDS_PAIRS ? eval_lds_bytes_pairs(t.N, t.K)
                                                 : eval_lds_bytes(t.N, t.K, false);
-  const LaunchShape ls = stream_shape(c, lds, vec ? n / 4 : 0, n, num_cu);
+  const LaunchShape ls = forward_shape(lds, vec ? n / 4 : 0, n, num_cu);
   const int v = (vec ? kVec : 0) | (g_locate == PWL_LOCATE_SEARCH ? kSearch : 0) | (ls.block << kBlockBit);
 #define PWL_FWD(UU, RR, OO) \
   hipLaunchKernelGGL((k_eval_fwd<UU, RR, OO>), dim3(ls.grid), dim3(ls.block), ls.lds, s, t, vo, x, y, n, v)
 #define PWL_FWD_U(RR, OO)                   \
-  switch (c.unroll) {                       \
+  switch (ls.unroll) {                      \
     case 1: PWL_FWD(1, RR, OO); break;      \
     case 2: PWL_FWD(2, RR, OO); break;      \
     default: PWL_FWD(4, RR, OO); break;     \
@@ -327,7 +370,13 @@ void launch_bwd_u(const LaunchShape& ls, int key, const EvalTable& t, const floa
 LaunchShape backward_shape(const EvalTable& t, const float* x, const float* g, const float* y, const float* dx,
                            bool wdv, int64_t n, int num_cu) {
   const bool vec = word_aligned(x) && word_aligned(g) && word_aligned(y) && word_aligned(dx);
-  return stream_shape(g_launch[1], eval_lds_bytes(t.N, t.K, wdv), vec ? n / 4 : 0, n, num_cu);
+  const LaunchConfig c = g_launch[PWL_KERNEL_BACKWARD];
+  const size_t lds = eval_lds_bytes(t.N, t.K, wdv);
+  const int64_t n4 = vec ? n / 4 : 0, v = (n4 + num_cu - 1) / num_cu;   // v: vectors per CU
+  if (is_small(c, n4, num_cu) && v <= 512)
+    return small_shape(c, 1, (v <= 256 && t.N <= 1024) ? 256 : 512, lds, n4, num_cu);
+  if (is_small(c, n4, num_cu) && v <= 1024) return small_shape(c, 2, 512, lds, n4, num_cu);
+  return stream_shape(c, lds, std::max<int64_t>(kMinPointsPerWG, kPointsPerStagedByte * (int64_t)lds), n4, n, num_cu);
 }
 
 size_t backward_workspace_floats(const EvalTable& t, const float* x, const float* g, const float* y,
@@ -341,7 +390,6 @@ hipError_t launch_eval_backward(const EvalTable& t, const float* vo, const float
                                 hipStream_t s) {
   const bool vec = word_aligned(x) && word_aligned(g) && word_aligned(y) && word_aligned(dx);
   const bool wdv = dv != nullptr;
-  const LaunchConfig c = g_launch[1];
   const LaunchShape ls = backward_shape(t, x, g, y, dx, wdv, n, num_cu);
   const int key = (y != nullptr ? 4 : 0) | (dx != nullptr ? 2 : 0) | (wdv ? 1 : 0);
   if (key == 0) return hipErrorInvalidValue;
@@ -351,7 +399,7 @@ hipError_t launch_eval_backward(const EvalTable& t, const float* vo, const float
   }
   if (wdv && part == nullptr) return hipErrorInvalidValue;
   const int v = (vec ? kVec : 0) | (ls.block << kBlockBit);
-  switch (c.unroll) {
+  switch (ls.unroll) {
     case 1: launch_bwd_u<1>(ls, key, t, vo, x, g, y, dx, part, n, v, s); break;
     case 2: launch_bwd_u<2>(ls, key, t, vo, x, g, y, dx, part, n, v, s); break;
     default: launch_bwd_u<4>(ls, key, t, vo, x, g, y, dx, part, n, v, s); break;
@@ -367,7 +415,10 @@ hipError_t launch_eval_backward(const EvalTable& t, const float* vo, const float
 
 hipError_t launch_locate(const EvalTable& t, const float* x, int32_t* seg, int64_t n, int num_cu,
                          hipStream_t s) {
-  const LaunchShape ls = stream_shape(g_launch[0], eval_lds_bytes(t.N, t.K, false), 0, n, num_cu);
+  const size_t lds = eval_lds_bytes(t.N, t.K, false);
+  const LaunchShape ls = stream_shape(g_launch[PWL_KERNEL_FORWARD], lds,
+                                      std::max<int64_t>(kMinPointsPerWG, kPointsPerStagedByte * (int64_t)lds), 0, n,
+                                      num_cu);
   const int v = (g_locate == PWL_LOCATE_SEARCH) ? kSearch : 0;
   hipLaunchKernelGGL(k_locate, dim3(ls.grid), dim3(ls.block), ls.lds, s, t, x, seg, n, v);
   return hipGetLastError();

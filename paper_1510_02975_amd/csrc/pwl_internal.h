@@ -135,6 +135,7 @@ struct LaunchShape {
   int block;
   int grid;
   size_t lds;
+  int unroll;
 };
 
 // Tunable launch configuration of a streaming kernel family.

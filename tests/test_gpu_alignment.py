@@ -96,3 +96,30 @@ def test_staging_sizes(N, shape):
         assert np.max(np.abs(yo.cpu().numpy() - yor)) <= 4e-6 * 1.5
         assert np.all(np.abs(dv.cpu().numpy() - dvr) <= GRAD_TOL * wk + 1e-30)
         t.free()
+
+
+@pytest.mark.parametrize("N", [64, 4096])
+@pytest.mark.parametrize("vectors_per_cu", [1, 256, 512, 768, 1024, 2048, 4096])
+def test_small_launch_edges(N, vectors_per_cu):
+    """Point counts one vector to either side of where the shape of a small
+    launch changes: every point and every gradient against the oracle."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    t = P.pwl_build(O.GAUSSIAN, (1.0, 1.0), -5.0, 5.0, N, O.OPTIMAL, O.PROJ)
+    d = P.pwl_table_download(t)
+    X, v = d["knots"].astype(np.float64), d["values"].astype(np.float64)
+    for n in (4 * cus * vectors_per_cu - 3, 4 * cus * vectors_per_cu, 4 * cus * vectors_per_cu + 5):
+        xh, gh = W.normal_points(n, 1.5, 5), W.upstream_grad(n, 6)
+        x64, g64 = xh.astype(np.float64), gh.astype(np.float64)
+        yr, _, dvr = O.evaluate_backward(X, v, x64, g64)
+        _, _, wk = O.evaluate_backward(X, np.zeros(len(X)), x64, np.abs(g64))
+        x, g = torch.from_numpy(xh).to(dev), torch.from_numpy(gh).to(dev)
+        y = P.pwl_eval(t, x)
+        yb, _, dv = P.pwl_eval_backward(t, x, g)
+        say("small launches N=%d n=%d" % (N, n))
+        assert np.max(np.abs(y.cpu().numpy() - yr)) <= Y_TOL
+        assert torch.equal(yb, y)
+        assert np.all(np.abs(dv.cpu().numpy() - dvr) <= GRAD_TOL * wk + 1e-30)
+    t.free()
