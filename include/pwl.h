@@ -239,8 +239,8 @@ pwl_status pwl_eval(const pwl_table* t, const float* v_override, const float* x,
  * (the paper gives none): dy/dx is the segment slope, dy/dv_k the hat weight.
  * Workspace: (workgroups x (N+1)) floats owned by the table, taken from
  * the stream-ordered allocator (hipMallocAsync on `stream`) by the first
- * call with dv that needs more; the old rows are released on `stream` after
- * their last user has finished, and the rows are freed with the table.
+ * call with dv that needs more (at least doubling); they are freed with the
+ * table, outgrown ones too.
  * Calls with dv on one table share them, so they must not overlap in time:
  * issue them on one stream.
  */

@@ -133,12 +133,21 @@ def _check(status):
         raise PWLError(status, msg.decode() if msg else "")
 
 
+# The current stream's handle and the current device straight from torch's
+# runtime bindings: torch.cuda.current_stream() builds a Stream object around
+# the same handle, 2.8 us of the 8.9 a small pwl_eval took.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
+        return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def _ptr(t, dtype=torch.float32, name="tensor"):
@@ -152,7 +161,7 @@ def _ptr(t, dtype=torch.float32, name="tensor"):
         raise ValueError("%s must be a device tensor" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _params(params):
@@ -299,21 +308,25 @@ def pwl_table_free(table):
 
 
 def pwl_eval(table, x, y=None, v_override=None, stream=None):
+    n = x.numel()
     if y is None:
         y = torch.empty_like(x)
-    if y.numel() != x.numel():
+    elif y.numel() != n:
         raise ValueError("y must have as many elements as x")
     if v_override is not None and v_override.numel() != table.N + 1:
         raise ValueError("v_override must have N + 1 elements")
-    _check(load_library().pwl_eval(table.handle, _ptr(v_override, name="v_override"), _ptr(x, name="x"),
-                                   _ptr(y, name="y"), x.numel(), _stream(stream)))
+    status = (_lib or load_library()).pwl_eval(table.handle, _ptr(v_override, name="v_override"), _ptr(x, name="x"),
+                                               _ptr(y, name="y"), n, _stream(stream))
+    if status != 0:
+        _check(status)
     return y
 
 
 def pwl_eval_backward(table, x, g, y=None, dx=None, dv=None, v_override=None, stream=None,
                       want=("y", "dx", "dv")):
     """Fused forward + backward; returns (y, dx, dv) with None for outputs not wanted."""
-    if g.numel() != x.numel():
+    n = x.numel()
+    if g.numel() != n:
         raise ValueError("g must have as many elements as x")
     if y is None and "y" in want:
         y = torch.empty_like(x)
@@ -321,13 +334,15 @@ def pwl_eval_backward(table, x, g, y=None, dx=None, dv=None, v_override=None, st
         dx = torch.empty_like(x)
     if dv is None and "dv" in want:
         dv = torch.empty(table.N + 1, dtype=torch.float32, device=x.device)
+    elif dv is not None and dv.numel() != table.N + 1:
+        raise ValueError("dv must have N + 1 elements")
     if v_override is not None and v_override.numel() != table.N + 1:
         raise ValueError("v_override must have N + 1 elements")
-    if dv is not None and dv.numel() != table.N + 1:
-        raise ValueError("dv must have N + 1 elements")
-    _check(load_library().pwl_eval_backward(
+    status = (_lib or load_library()).pwl_eval_backward(
         table.handle, _ptr(v_override, name="v_override"), _ptr(x, name="x"), _ptr(g, name="g"),
-        _ptr(y, name="y"), _ptr(dx, name="dx"), _ptr(dv, name="dv"), x.numel(), _stream(stream)))
+        _ptr(y, name="y"), _ptr(dx, name="dx"), _ptr(dv, name="dv"), n, _stream(stream))
+    if status != 0:
+        _check(status)
     return y, dx, dv
 
 

@@ -41,11 +41,14 @@ struct pwl_table {
   hipEvent_t built = nullptr;   // recorded after every build of the table
   // dL/dv partial sums of the fused backward (one row per workgroup), taken
   // from the stream-ordered allocator by the first backward call that needs
-  // more; part_used is recorded after every launch that reads them
+  // more.  Outgrown rows, which calls on other streams may still read, are
+  // kept with the table: a capacity at least doubles, so together they stay
+  // below the current one, and no call has to record an event for them.
   mutable std::mutex part_mu;
   mutable float* part = nullptr;
   mutable size_t part_cap = 0;   // floats
-  mutable hipEvent_t part_used = nullptr;
+  mutable float* outgrown[64] = {};
+  mutable int noutgrown = 0;
 };
 
 namespace {
@@ -554,12 +557,12 @@ pwl_status pwl_table_download(const pwl_table* t, float* knots, float* values, d
 void pwl_table_free(pwl_table* t) {
   if (t == nullptr) return;
   if (t->part != nullptr) {
-    // stream-ordered memory: released after its last user, then waited for
-    (void)hipEventSynchronize(t->part_used);
+    // stream-ordered memory: released once the device is done with it
+    (void)hipDeviceSynchronize();
     (void)hipFreeAsync(t->part, g_aux[t->device]);
+    for (int i = 0; i < t->noutgrown; ++i) (void)hipFreeAsync(t->outgrown[i], g_aux[t->device]);
     (void)hipStreamSynchronize(g_aux[t->device]);
   }
-  if (t->part_used) (void)hipEventDestroy(t->part_used);
   if (t->built) (void)hipEventDestroy(t->built);
   (void)hipFree(t->base);
   delete t;
@@ -595,29 +598,29 @@ pwl_status pwl_eval_backward(const pwl_table* t, const float* v_override, const 
     PWL_HIP(pwl::launch_eval_backward(e, v_override, x, g, y, dx, dv, nullptr, n, num_cu, s));
     return PWL_OK;
   }
-  // The partial-sum rows: grown in stream order on the caller's stream (the
-  // old rows are released once their last user - on whatever stream - has
-  // finished), never by a device-wide synchronisation.
+  // The partial-sum rows: grown in stream order on the caller's stream,
+  // never by a device-wide synchronisation.
   std::lock_guard<std::mutex> lock(t->part_mu);
   const size_t need = pwl::backward_workspace_floats(e, x, g, y, dx, n, num_cu);
   if (need > t->part_cap) {
-    if (t->part != nullptr) {
-      PWL_HIP(hipStreamWaitEvent(s, t->part_used, 0));
-      PWL_HIP(hipFreeAsync(t->part, s));
-      t->part = nullptr;
-      t->part_cap = 0;
-    }
-    if (t->part_used == nullptr) PWL_HIP(hipEventCreateWithFlags(&t->part_used, hipEventDisableTiming));
+    if (t->noutgrown == (int)(sizeof(t->outgrown) / sizeof(t->outgrown[0])))
+      return fail(PWL_ENOMEM, "the dL/dv partial sums were outgrown too often");
+    size_t cap = std::max(need, 2 * t->part_cap);
     void* p = nullptr;
-    hipError_t me = hipMallocAsync(&p, need * sizeof(float), s);
+    hipError_t me = hipMallocAsync(&p, cap * sizeof(float), s);
+    if (me != hipSuccess && cap > need) {
+      (void)hipGetLastError();
+      cap = need;
+      me = hipMallocAsync(&p, cap * sizeof(float), s);
+    }
     if (me != hipSuccess)
-      return fail(PWL_ENOMEM, "hipMallocAsync(%zu) for the dL/dv partial sums failed: %s", need * sizeof(float),
+      return fail(PWL_ENOMEM, "hipMallocAsync(%zu) for the dL/dv partial sums failed: %s", cap * sizeof(float),
                   hipGetErrorString(me));
+    if (t->part != nullptr) t->outgrown[t->noutgrown++] = t->part;
     t->part = static_cast<float*>(p);
-    t->part_cap = need;
+    t->part_cap = cap;
   }
   PWL_HIP(pwl::launch_eval_backward(e, v_override, x, g, y, dx, dv, t->part, n, num_cu, s));
-  PWL_HIP(hipEventRecord(t->part_used, s));
   return PWL_OK;
 }
 
