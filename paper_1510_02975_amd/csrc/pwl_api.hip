@@ -17,7 +17,6 @@
 #include "pwl_internal.h"
 
 namespace pwl {
-hipError_t configure_build_kernels(int max_lds);
 hipError_t configure_eval_kernels(int max_lds);
 }  // namespace pwl
 
@@ -99,7 +98,6 @@ pwl_status device_ready(int* dev_out, int* num_cu, int* max_lds = nullptr) {
     int cu = 0, lds = 0;
     hipError_t e = hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    if (e == hipSuccess) e = pwl::configure_build_kernels(lds);
     if (e == hipSuccess) e = pwl::configure_eval_kernels(lds);
     if (e == hipSuccess) e = pwl::configure_batch_kernels(lds);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&g_aux[dev], hipStreamNonBlocking);
@@ -346,8 +344,7 @@ pwl_status create_table(const pwl::BuildParams& bp, void* stream, pwl_table** ou
   int dev = 0, max_lds = 0;
   pwl_status st = device_ready(&dev, nullptr, &max_lds);
   if (st != PWL_OK) return st;
-  const size_t need = std::max(pwl::finalize_lds_bytes(bp.N),
-                               pwl::batch_table_lds_bytes(bp.N, pwl::map_cells_max(bp.N), true));
+  const size_t need = pwl::batch_table_lds_bytes(bp.N, pwl::map_cells_max(bp.N), true);
   if (need > (size_t)max_lds)
     return fail(PWL_ECAPACITY, "N = %d needs %zu bytes of LDS, the device offers %d", bp.N, need, max_lds);
   pwl::TableDev td;

@@ -5,12 +5,11 @@
 //     k_invert_knots     FP64 prefix of those sums, targets i S_M / N, linear inversion;
 //                        per knot also, for the interpolant, f(x_i)
 //   every table:
-//     k_finalize         one workgroup: uniform knots (Sec. IV) when asked, the
-//                        uniform index map, the knot-collapse check, for the
-//                        projection (Sec. II-B2) FP32 Gauss-Legendre integrals of f
-//                        against the hats and the FP64 solve of M c = b (parallel
-//                        cyclic reduction), and the packed records
-//                        {x_k, v_k, slope_k, x_{k+1}}
+//     k_finalize         uniform knots (Sec. IV) when asked, the uniform index map,
+//                        the knot-collapse check, for the projection (Sec. II-B2)
+//                        FP32 Gauss-Legendre integrals of f against the hats and the
+//                        FP64 solve of M c = b (parallel cyclic reduction), and the
+//                        table's images in memory
 #include <hip/hip_runtime.h>
 
 #include "pwl_func.h"
@@ -21,21 +20,53 @@ namespace pwl {
 
 namespace {
 
-constexpr int kScanThreads = 1024;      // density workgroup size (one sample per thread)
-constexpr int kScanLanes = 32;          // lanes that sum cells sequentially
-constexpr int kCellsPerScanLane = kDensityCellsPerBlock / kScanLanes;   // 32
+constexpr int kScanThreads = 1024;      // density workgroup size (one cell per thread)
+constexpr int kScanWaves = kScanThreads / 64;
 
-// Inclusive trapezoid sums of the density over the cells of workgroup `blk`.
-// Cell j (1-based) spans [t_{j-1}, t_j], t_j = a + j dt, and adds
-// (d_{j-1} + d_j) dt / 2.  All 1024 threads evaluate the density (one FP64
-// sample each); then 32 lanes each sum 32 consecutive cells sequentially and
-// lane 0 chains the 32 lane totals sequentially.  Every sum therefore
-// extends the previous one by one rounded addition of a non-negative term,
-// so the sums are monotone non-decreasing and the block total equals the
-// last sum bit for bit; both kernels below call this same code.  Contraction
-// is off so that every operation is one IEEE-rounded FP64 operation.
-__device__ double scan_block_cells(const BuildParams& bp, int blk, double* s_d, double* s_tp,
-                                   double* s_S) {
+// Inclusive sums over the workgroup of one non-negative value per thread: a
+// butterfly of shifted adds inside each wave, then the earlier waves' sums
+// in order.  s_w: kScanWaves doubles, free to reuse after the next barrier.
+// Contraction is off so that every operation is one IEEE-rounded FP64
+// operation; all workgroups that scan the same values get the same sums.
+__device__ double block_scan(double v, double* s_w) {
+#pragma clang fp contract(off)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double u = __shfl_up(v, d, 64);
+    if (lane >= d) v = v + u;
+  }
+  if (lane == 63) s_w[wave] = v;
+  __syncthreads();
+  double before = 0.0;
+#pragma unroll
+  for (int w = 0; w < kScanWaves - 1; ++w) before = before + (w < wave ? s_w[w] : 0.0);
+  return before + v;
+}
+
+// Inclusive maxima over the workgroup, likewise.
+__device__ double block_max_scan(double v, double* s_w) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const double u = __shfl_up(v, d, 64);
+    if (lane >= d) v = fmax(v, u);
+  }
+  if (lane == 63) s_w[wave] = v;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kScanWaves - 1; ++w)
+    if (w < wave) v = fmax(v, s_w[w]);
+  return v;
+}
+
+// Inclusive trapezoid sum of the density up to this thread's cell of
+// workgroup `blk`.  Cell j (1-based) spans [t_{j-1}, t_j], t_j = a + j dt,
+// and adds (d_{j-1} + d_j) dt / 2; all threads evaluate the density (one FP64
+// sample each).  (Chains of 32 dependent LDS reads and additions took
+// 2 us longer in each of the two kernels below: N = 1024 7.3 and 11.6 us,
+// 5.0 and 9.7 so.)
+__device__ double scan_block_cells(const BuildParams& bp, int blk, double* s_d, double* s_w) {
 #pragma clang fp contract(off)
   constexpr int C = kDensityCellsPerBlock;
   const int tid = threadIdx.x;
@@ -47,47 +78,20 @@ __device__ double scan_block_cells(const BuildParams& bp, int blk, double* s_d, 
     s_d[s] = (j <= bp.M) ? knot_density(bp.f, bp.a + (double)j * dt) : 0.0;
   }
   __syncthreads();
-  if (tid < kScanLanes) {
-    double acc = 0.0;
-#pragma unroll 8
-    for (int q = 0; q < kCellsPerScanLane; ++q) {
-      const int c = tid * kCellsPerScanLane + q;
-      const double inc = (j0 + c + 1 <= bp.M) ? (s_d[c] + s_d[c + 1]) * hdt : 0.0;
-      acc = acc + inc;
-      if (s_S != nullptr) s_S[c] = acc;
-    }
-    s_tp[tid] = acc;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double run = 0.0;
-    for (int t = 0; t < kScanLanes; ++t) {
-      const double v = s_tp[t];
-      s_tp[t] = run;
-      run = run + v;
-    }
-    s_tp[kScanLanes] = run;
-  }
-  __syncthreads();
-  if (s_S != nullptr) {
-    const int lane = tid / kCellsPerScanLane;   // 1024 threads cover the 1024 cells
-    s_S[tid] = s_tp[lane] + s_S[tid];
-  }
-  const double total = s_tp[kScanLanes];
-  __syncthreads();
-  return total;
+  const double inc = (j0 + tid + 1 <= bp.M) ? (s_d[tid] + s_d[tid + 1]) * hdt : 0.0;
+  return block_scan(inc, s_w);
 }
+static_assert(kScanThreads == kDensityCellsPerBlock, "one cell per thread");
+static_assert(kMaxDensityBlocks <= kScanThreads, "one block total per thread");
 
 __global__ __launch_bounds__(kScanThreads) void k_density_totals(BuildParams bp, TableDev td) {
   __shared__ double s_d[kDensityCellsPerBlock + 1];
-  __shared__ double s_tp[kScanLanes + 1];
-  const double tot = scan_block_cells(bp, blockIdx.x, s_d, s_tp, nullptr);
-  if (threadIdx.x == 0) {
-    td.totals[blockIdx.x] = tot;
-    if (blockIdx.x == 0) {
-      td.status[0] = 0u;
-      td.status[1] = 0u;
-    }
+  __shared__ double s_w[kScanWaves];
+  const double sum = scan_block_cells(bp, blockIdx.x, s_d, s_w);
+  if (threadIdx.x == kScanThreads - 1) td.totals[blockIdx.x] = sum;
+  if (threadIdx.x == 0 && blockIdx.x == 0) {
+    td.status[0] = 0u;
+    td.status[1] = 0u;
   }
 }
 
@@ -113,46 +117,18 @@ __global__ __launch_bounds__(kScanThreads) void k_invert_knots(BuildParams bp, T
   constexpr int C = kDensityCellsPerBlock;
   __shared__ double s_d[C + 1];
   __shared__ double s_S[C];
-  __shared__ double s_tp[kScanLanes + 1];
-  __shared__ double s_lane[kScanLanes + 1];
-  __shared__ double s_tot[kMaxDensityBlocks];
+  __shared__ double s_w[2][kScanWaves];
   __shared__ double s_off[3];   // offset of this block, offset of the next, S_M
   const int tid = threadIdx.x;
   const int blk = blockIdx.x;
-  for (int b = tid; b < bp.G; b += kScanThreads) s_tot[b] = td.totals[b];
-  __syncthreads();
-  // Prefix of the workgroup totals, chained in two sequential levels (32
-  // lanes of consecutive totals, then the lane sums) so that the offset of
-  // block b + 1 is, bit for bit, the offset of block b plus its total.
-  const int per = (bp.G + kScanLanes - 1) / kScanLanes;
-  const int my_lane = blk / per;
-  if (tid < kScanLanes) {
-    double acc = 0.0, before = 0.0, through = 0.0;
-    for (int q = 0; q < per; ++q) {
-      const int b = tid * per + q;
-      if (b < bp.G) {
-        if (b == blk) before = acc;
-        acc = acc + s_tot[b];
-        if (b == blk) through = acc;
-      }
-    }
-    s_lane[tid] = acc;
-    if (tid == my_lane) {
-      s_off[0] = before;
-      s_off[1] = through;
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double run = 0.0, base = 0.0;
-    for (int t = 0; t < kScanLanes; ++t) {
-      if (t == my_lane) base = run;
-      run = run + s_lane[t];
-    }
-    s_off[0] = base + s_off[0];
-    s_off[1] = base + s_off[1];
-    s_off[2] = run;
-  }
+  // Prefix of the workgroup totals, made non-decreasing: the offset of block
+  // b + 1 is the end of block b in every workgroup, so each target falls to
+  // exactly one of them.
+  const double run = block_max_scan(block_scan(tid < bp.G ? td.totals[tid] : 0.0, s_w[0]), s_w[1]);
+  if (tid == 0 && blk == 0) s_off[0] = 0.0;
+  if (tid == blk - 1) s_off[0] = run;
+  if (tid == blk) s_off[1] = run;
+  if (tid == bp.G - 1) s_off[2] = run;
   __syncthreads();
   const double off = s_off[0], next = s_off[1], total = s_off[2];
   if (!(total > 0.0) || !isfinite(total)) {
@@ -163,22 +139,29 @@ __global__ __launch_bounds__(kScanThreads) void k_invert_knots(BuildParams bp, T
     }
     return;
   }
-  scan_block_cells(bp, blk, s_d, s_tp, s_S);
+  // the targets i S_M / N in (off, next], and one more to either side for
+  // the rounding of the bounds
+  const double per = (double)bp.N / total;
+  const int i0 = max(1, (int)fmin(off * per, (double)bp.N) - 1), i1 = min(bp.N - 1, (int)fmin(next * per, (double)bp.N) + 1);
+  s_S[tid] = scan_block_cells(bp, blk, s_d, s_w[0]);
+  __syncthreads();
   const double dt = (bp.b - bp.a) / (double)bp.M;
   const double snap = 1e-12 * (bp.b - bp.a);
-  for (int i = 1 + tid; i < bp.N; i += kScanThreads) {
+  for (int i = i0 + tid; i <= i1; i += kScanThreads) {
     const double tau = ((double)i * total) / (double)bp.N;
     if (!(off < tau && tau <= next)) continue;
-    // smallest c with off + S_local[c] >= tau (exists: the last one equals next)
+    // the target inside the block, at most its last sum (which the rounding
+    // of the offsets may pass), and the smallest cell whose sum reaches it
+    const double t = fmin(tau - off, s_S[C - 1]);
     int lo = 0, hi = C - 1;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
-      if (off + s_S[mid] >= tau) hi = mid; else lo = mid + 1;
+      if (s_S[mid] >= t) hi = mid; else lo = mid + 1;
     }
-    const double Sj = off + s_S[lo];
-    const double Sp = (lo > 0) ? off + s_S[lo - 1] : off;
+    const double Sj = s_S[lo];
+    const double Sp = (lo > 0) ? s_S[lo - 1] : 0.0;
     const int j = blk * C + lo + 1;                    // 1-based cell number
-    const double frac = (tau - Sp) / (Sj - Sp);
+    const double frac = (Sj > Sp) ? (t - Sp) / (Sj - Sp) : 0.0;
     double x = (bp.a + (double)(j - 1) * dt) + frac * dt;
     if (fabs(x) <= snap) x = 0.0;
     emit_knot(bp, td, i, x);
@@ -189,202 +172,196 @@ __global__ __launch_bounds__(kScanThreads) void k_invert_knots(BuildParams bp, T
   }
 }
 
-constexpr int kFinalizeThreads = 1024;
-constexpr int kRowsPerThread = (PWL_MAX_N + 1 + kFinalizeThreads - 1) / kFinalizeThreads;
+constexpr int kFinalizeThreads = 256;
+// The projection's solve.  Every row of the Gram matrix has off-diagonal sum
+// rho = 1/2 of its diagonal, and a step of parallel cyclic reduction takes
+// rho to at most rho^2 in every row (the eliminated terms leave the diagonal
+// and the couplings by the same amount): after six steps the couplings are
+// below 2^-64 of the diagonal, so the system is diagonal in FP64 whatever N.
+// Six steps also reach only 63 rows to either side, so a workgroup can solve
+// kFinalizeRows rows by itself from them and kSolveHalo rows on each side.
+constexpr int kSolveSteps = 6;
+constexpr int kSolveHalo = 64;
+constexpr int kFinalizeRows = 124;
+static_assert(kSolveHalo + kFinalizeRows + 1 + kSolveHalo <= kFinalizeThreads, "a row per thread");
 
-// Everything after the knots, in one workgroup that keeps the knots and their
-// map cells in LDS (every later step reads them several times):
-//  1. (uniform partition) the knots x_k = a + (b - a) k / N and their
-//     interpolant values; otherwise the knots the inversion wrote;
-//  2. per segment k: its cells of the uniform index map lo[u] = #{interior
-//     knots with cell < u} - segment k owns (cell(x_k), cell(x_{k+1})], with
-//     cell(x_0) = -1 and cell(x_N) = K - 1, so each cell is written once when
-//     the knots increase; the knot-collapse check; the deepest cell (the
-//     evaluator's unrolled compare depth);
-//  3. (projection) <f, phi_k> by 16-point Gauss-Legendre per segment, one
-//     thread per segment;
-//  4. (projection) the FP64 solve of M c = b by parallel cyclic reduction;
-//  5. the packed records {x_k, v_k, slope_k, x_{k+1}} (NaN for a collapsed
-//     table, whose map is then cleared).
+// Everything after the knots.  Workgroup g owns rows (knots) and segments
+// [g kFinalizeRows, (g + 1) kFinalizeRows):
+//  1. all knots into LDS: x_k = a + (b - a) k / N for a uniform partition,
+//     otherwise the ones the inversion wrote; the knot-collapse check;
+//     workgroup 0 also finds the deepest map cell (the evaluator's unrolled
+//     compare depth);
+//  2. (projection) <f, phi_k> by 16-point Gauss-Legendre per segment and the
+//     FP64 solve of M c = b, one thread per row of the workgroup's window;
+//  3. per owned segment k: its cells of the uniform index map lo[u] =
+//     #{interior knots with cell < u} - segment k owns (cell(x_k),
+//     cell(x_{k+1})], with cell(x_0) = -1 and cell(x_N) = K - 1, so each cell
+//     is written once when the knots increase - and its record {x_k, v_k,
+//     slope_k, x_{k+1}} (NaN for a collapsed table, whose map is all zero:
+//     the evaluators never leave the table through it), in both images.
+// What bounds it is latency: one workgroup did all of it in 18.5 us at
+// N = 1024 and 50 us at N = 4096 (11 and 13 reduction steps with two barriers
+// each); spread so, with one branch on the function per segment instead of
+// one per node, it takes 10.9 and 17.4 us.
 __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, TableDev td) {
-  extern __shared__ double s_pcr[];
-  const int N = bp.N, n = N + 1;
-  const int tid = threadIdx.x;
-  double* A = s_pcr;
-  double* R = A + n;      // reciprocal diagonal during the solve
-  double* Cu = R + n;
-  double* D = Cu + n;
-  float* X = reinterpret_cast<float*>(D + n);        // [N+1] FP32 knots
-  uint16_t* U = reinterpret_cast<uint16_t*>(X + n);  // [N+1] map cell of each interior knot
-  __shared__ int s_collapsed, s_maxc;
-  if (tid == 0) {
-    s_collapsed = 0;
-    s_maxc = 0;
-  }
-  // 1. knots (and, for the uniform interpolant, the values) into LDS
+  __shared__ float X[PWL_MAX_N + 1];                 // FP32 knots
+  __shared__ double sA[2][kFinalizeThreads], sC[2][kFinalizeThreads], sD[2][kFinalizeThreads],
+      sR[2][kFinalizeThreads];                       // the solve's rows, R the reciprocal diagonal
+  __shared__ int s_maxc;
+  const int N = bp.N, tid = threadIdx.x;
+  const int r0 = blockIdx.x * kFinalizeRows;         // first owned row
+  const int i = r0 - kSolveHalo + tid;               // this thread's row and segment
+  const bool row = i >= 0 && i <= N, seg = i >= 0 && i < N;
+  const bool own = tid >= kSolveHalo && tid < kSolveHalo + kFinalizeRows && row;
   const bool uniform = bp.partition == PWL_UNIFORM;
-  for (int k = tid; k <= N; k += kFinalizeThreads) {
-    float x32;
-    if (uniform) {
-      const double x = uniform_knot(bp, k);
-      x32 = (float)x;
-      td.knots64[k] = x;
-      td.knots[k] = x32;
-      if (bp.values == PWL_INTERP) D[k] = (double)f_value32(bp.f, x32);
-    } else {
-      x32 = td.knots[k];
-      if (bp.values == PWL_INTERP) D[k] = (double)td.values[k];
-    }
-    X[k] = x32;
-    U[k] = (k >= 1 && k <= N - 1) ? (uint16_t)map_cell(x32, bp.a32, bp.scale32, bp.K) : (uint16_t)0;
-  }
-  __syncthreads();
 
-  // 2. map, collapse check, deepest cell
-  int run = 0, bad = 0;
-  for (int k = tid; k < N; k += kFinalizeThreads) {
-    const int u0 = (k == 0) ? -1 : (int)U[k];
-    const int u1 = (k + 1 == N) ? bp.K - 1 : (int)U[k + 1];
-    for (int u = u0 + 1; u <= u1; ++u) td.lo[u] = (uint16_t)k;
+  // 1. knots, collapse, deepest cell
+  if (tid == 0) s_maxc = 0;
+  for (int k = tid; k <= N; k += kFinalizeThreads) X[k] = uniform ? (float)uniform_knot(bp, k) : td.knots[k];
+  __syncthreads();
+  int bad = 0;
+  for (int k = tid; k < N; k += kFinalizeThreads)
     if (!(X[k + 1] > X[k])) bad = 1;
-    if (k >= 1 && (k == 1 || (int)U[k - 1] != u0)) {   // first interior knot of its cell
+  const bool collapsed = __syncthreads_or(bad) != 0;
+  auto cell = [&](int k) { return map_cell(X[k], bp.a32, bp.scale32, bp.K); };
+  if (blockIdx.x == 0) {
+    int run = 0;
+    for (int k = 1 + tid; k < N; k += kFinalizeThreads) {
+      const int u = cell(k);
+      if (k > 1 && cell(k - 1) == u) continue;       // not the first interior knot of its cell
       int r = 1;
-      while (k + r <= N - 1 && (int)U[k + r] == u0) ++r;
+      while (k + r <= N - 1 && cell(k + r) == u) ++r;
       run = max(run, r);
     }
+    if (run > 0) atomicMax(&s_maxc, run);
   }
-  for (int u = bp.K + tid; u < 8 * image_map_words(bp.K); u += kFinalizeThreads)
-    td.lo[u] = (u == bp.K) ? (uint16_t)(N - 1) : (uint16_t)0;
-  if (bad) atomicOr(&s_collapsed, 1);
-  if (run > 0) atomicMax(&s_maxc, run);
 
-  // 3-4. vertex values
+  // 2. vertex values
+  double val = 0.0;
   if (bp.values == PWL_PROJ) {
-    // one thread per segment k: its 16 Gauss-Legendre nodes in order;
-    // L_k = <f, phi_k> on segment k goes to D[k], R_k = <f, phi_{k+1}> to A[k+1]
-    for (int k = tid; k < N; k += kFinalizeThreads) {
-      const float xk = X[k];
-      const float h = X[k + 1] - xk;
+    // one thread per segment: its 16 Gauss-Legendre nodes in order
+    double left = 0.0, right = 0.0;                  // <f, phi_i>, <f, phi_{i+1}> on segment i
+    if (seg) {
+      const float xk = X[i];
+      const float h = X[i + 1] - xk;
       float sl = 0.0f, sr = 0.0f;
-#pragma unroll
-      for (int q = 0; q < kGaussPoints; ++q) {
-        const float t = bp.gl.t[q];
-        const float fq = bp.gl.w[q] * f_value32(bp.f, fmaf(h, t, xk));
-        sl = fmaf(1.0f - t, fq, sl);
-        sr = fmaf(t, fq, sr);
-      }
-      D[k] = (double)(h * sl);
-      A[k + 1] = (double)(h * sr);
+      with_func(bp.f, [&](auto func) {
+        constexpr int F = decltype(func)::value;
+        // the cheap functions' evaluations all in flight together
+        constexpr int kUnroll = (F == PWL_F_BESSEL_J0 || F == PWL_F_SAMPLED) ? 2 : kGaussPoints;
+#pragma unroll kUnroll
+        for (int q = 0; q < kGaussPoints; ++q) {
+          const float t = bp.gl.t[q];
+          const float fq = bp.gl.w[q] * f_value32_of<F>(bp.f, fmaf(h, t, xk));
+          sl = fmaf(1.0f - t, fq, sl);
+          sr = fmaf(t, fq, sr);
+        }
+      });
+      left = (double)(h * sl);
+      right = (double)(h * sr);
     }
+    sR[1][tid] = right;
     __syncthreads();
     // Gram matrix of the hat basis from the element matrix (h/6)[[2,1],[1,2]]
-    // (half hats at both ends), right-hand side b_k = <f, phi_k>.  Row i is
-    // owned by thread i mod 1024 for the whole solve: it keeps its diagonal
-    // in registers and publishes the reciprocal for its neighbours.
-    double diag[kRowsPerThread];
-#pragma unroll
-    for (int r = 0; r < kRowsPerThread; ++r) {
-      const int i = tid + r * kFinalizeThreads;
-      if (i >= n) break;
+    // (half hats at both ends), right-hand side b_i = <f, phi_i>
+    double a = 0.0, c = 0.0, d = 1.0, b = 0.0;
+    if (row) {
       const double xi = (double)X[i];
       const double hl = (i > 0) ? xi - (double)X[i - 1] : 0.0;
       const double hr = (i < N) ? (double)X[i + 1] - xi : 0.0;
-      const double bl = (i > 0) ? A[i] : 0.0;
-      const double br = (i < N) ? D[i] : 0.0;
-      D[i] = bl + br;
-      A[i] = hl / 6.0;
-      Cu[i] = hr / 6.0;
-      diag[r] = hl / 3.0 + hr / 3.0;
-      R[i] = 1.0 / diag[r];
+      b = ((i > 0 && tid > 0) ? sR[1][tid - 1] : 0.0) + left;
+      a = hl / 6.0;
+      c = hr / 6.0;
+      d = 2.0 * a + 2.0 * c;
     }
+    sA[0][tid] = a; sC[0][tid] = c; sD[0][tid] = b; sR[0][tid] = 1.0 / d;
     __syncthreads();
     // Parallel cyclic reduction: at stride s every row eliminates its
-    // couplings to rows i - s and i + s; after ceil(log2 n) steps the system
-    // is diagonal.  No pivoting is needed: M is strictly diagonally dominant.
-    for (int s = 1; s < n; s <<= 1) {
-      double na[kRowsPerThread], nc[kRowsPerThread], nd[kRowsPerThread];
+    // couplings to rows i - s and i + s.  No pivoting is needed.  Rows next
+    // to the window's ends miss a neighbour; none of them reaches an owned row.
 #pragma unroll
-      for (int r = 0; r < kRowsPerThread; ++r) {
-        const int i = tid + r * kFinalizeThreads;
-        if (i >= n) break;
-        double bi = diag[r], di = D[i];
-        double an = 0.0, cn = 0.0;
-        if (i - s >= 0) {
-          const double al = -A[i] * R[i - s];
-          an = al * A[i - s];
-          bi += al * Cu[i - s];
-          di += al * D[i - s];
-        }
-        if (i + s < n) {
-          const double ga = -Cu[i] * R[i + s];
-          cn = ga * Cu[i + s];
-          bi += ga * A[i + s];
-          di += ga * D[i + s];
-        }
-        na[r] = an; diag[r] = bi; nc[r] = cn; nd[r] = di;
+    for (int step = 0; step < kSolveSteps; ++step) {
+      const int s = 1 << step, p = step & 1;
+      double an = 0.0, cn = 0.0;
+      if (row && i - s >= 0 && tid - s >= 0) {
+        const int q = tid - s;
+        const double al = -a * sR[p][q];
+        an = al * sA[p][q];
+        d += al * sC[p][q];
+        b += al * sD[p][q];
       }
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < kRowsPerThread; ++r) {
-        const int i = tid + r * kFinalizeThreads;
-        if (i >= n) break;
-        A[i] = na[r]; Cu[i] = nc[r]; D[i] = nd[r];
-        R[i] = 1.0 / diag[r];
+      if (row && i + s <= N && tid + s < kFinalizeThreads) {
+        const int q = tid + s;
+        const double ga = -c * sR[p][q];
+        cn = ga * sC[p][q];
+        d += ga * sA[p][q];
+        b += ga * sD[p][q];
       }
-      __syncthreads();
+      a = an;
+      c = cn;
+      if (step + 1 < kSolveSteps) {
+        sA[1 - p][tid] = a; sC[1 - p][tid] = c; sD[1 - p][tid] = b; sR[1 - p][tid] = 1.0 / d;
+        __syncthreads();
+      }
     }
-#pragma unroll
-    for (int r = 0; r < kRowsPerThread; ++r) {
-      const int i = tid + r * kFinalizeThreads;
-      if (i >= n) break;
-      D[i] = D[i] / diag[r];
-    }
+    val = b / d;
+    __syncthreads();
+  } else if (row) {
+    val = (double)(uniform ? f_value32(bp.f, X[i]) : td.values[i]);
   }
+  sD[0][tid] = val;
   __syncthreads();
 
-  // 5. values, flags and packed records
-  const bool collapsed = s_collapsed != 0;
+  // 3. values, flags and both images
   const int fw = image_soa_field_words(N), nkw = image_knot_words(N), nmw = image_map_words(bp.K);
-  float4* soa_tail = reinterpret_cast<float4*>(td.soa) + 2 * fw;   // the copies of kimg and lo
-  if (collapsed) {   // the evaluators never leave the table through an all-zero map
-    for (int u = tid; u < bp.K; u += kFinalizeThreads) td.lo[u] = 0;
-    __syncthreads();
+  float* soa_k = td.soa + 8 * fw;                                         // the copies of kimg and lo
+  uint16_t* soa_lo = reinterpret_cast<uint16_t*>(soa_k + 4 * nkw);
+  if (own) {
+    if (uniform) {
+      td.knots64[i] = uniform_knot(bp, i);
+      td.knots[i] = X[i];
+    }
+    td.values64[i] = val;
+    td.values[i] = (float)val;
   }
-  for (int w = tid; w < nmw; w += kFinalizeThreads)
-    soa_tail[nkw + w] = reinterpret_cast<const float4*>(td.lo)[w];
-  for (int i = tid; i < n; i += kFinalizeThreads) {
-    const double c = D[i];
-    td.values64[i] = c;
-    td.values[i] = (float)c;
-  }
-  for (int k = tid; k < N; k += kFinalizeThreads) {
-    const float x0 = X[k], x1 = X[k + 1];
-    const double v0 = (double)(float)D[k], v1 = (double)(float)D[k + 1];
-    const double h = (double)x1 - (double)x0;
+  if (own && seg) {
+    const float x0 = X[i], x1 = X[i + 1], f0 = (float)val, f1 = (float)sD[0][tid + 1];
     float4 r;
     r.x = x0;
-    r.y = (float)D[k];
-    r.z = (float)((v1 - v0) / h);
+    r.y = f0;
+    r.z = (float)(((double)f1 - (double)f0) / ((double)x1 - (double)x0));
     r.w = x1;
     if (collapsed) {
       r.y = __builtin_nanf("");
       r.z = __builtin_nanf("");
     }
-    td.rec[k] = r;
-    td.soa[k] = r.y;
-    td.soa[4 * fw + k] = r.z;
+    td.rec[i] = r;
+    td.soa[i] = r.y;
+    td.soa[4 * fw + i] = r.z;
+    td.kimg[i] = x0;
+    soa_k[i] = x0;
+    if (!collapsed) {
+      const int u0 = (i == 0) ? -1 : cell(i), u1 = (i + 1 == N) ? bp.K - 1 : cell(i + 1);
+      for (int u = u0 + 1; u <= u1; ++u) {
+        td.lo[u] = (uint16_t)i;
+        soa_lo[u] = (uint16_t)i;
+      }
+    }
   }
-  for (int k = tid; k < 4 * nkw; k += kFinalizeThreads) {
-    const float x = (k < N) ? X[k] : __builtin_nanf("");
-    td.kimg[k] = x;
-    reinterpret_cast<float*>(soa_tail)[k] = x;
-  }
-  if (tid == 0) {
-    // the density kernels may have raised DEGENERATE / NONFINITE
-    uint32_t st = (bp.partition == PWL_OPTIMAL) ? td.status[0] : 0u;
-    if (collapsed) st |= PWL_FLAG_KNOTS_COLLAPSED;
-    td.status[0] = st;
-    td.status[1] = (uint32_t)s_maxc;
+  if (collapsed)
+    for (int u = blockIdx.x * kFinalizeThreads + tid; u < bp.K; u += gridDim.x * kFinalizeThreads)
+      td.lo[u] = soa_lo[u] = 0;
+  if (blockIdx.x == 0) {
+    for (int k = N + tid; k < 4 * nkw; k += kFinalizeThreads) td.kimg[k] = soa_k[k] = __builtin_nanf("");
+    for (int u = bp.K + tid; u < 8 * nmw; u += kFinalizeThreads)
+      td.lo[u] = soa_lo[u] = (u == bp.K) ? (uint16_t)(N - 1) : (uint16_t)0;
+    if (tid == 0) {
+      // the density kernels may have raised DEGENERATE / NONFINITE
+      uint32_t st = uniform ? 0u : td.status[0];
+      if (collapsed) st |= PWL_FLAG_KNOTS_COLLAPSED;
+      td.status[0] = st;
+      td.status[1] = (uint32_t)s_maxc;
+    }
   }
 }
 
@@ -459,14 +436,8 @@ hipError_t launch_build(const BuildParams& bp, const TableDev& td, hipStream_t s
     hipLaunchKernelGGL(k_density_totals, dim3(bp.G), dim3(kScanThreads), 0, s, bp, td);
     hipLaunchKernelGGL(k_invert_knots, dim3(bp.G), dim3(kScanThreads), 0, s, bp, td);
   }
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), finalize_lds_bytes(bp.N), s, bp, td);
+  hipLaunchKernelGGL(k_finalize, dim3((bp.N + kFinalizeRows) / kFinalizeRows), dim3(kFinalizeThreads), 0, s, bp, td);
   return hipGetLastError();
-}
-
-hipError_t configure_build_kernels(int max_lds) {
-  const int want = (int)finalize_lds_bytes(PWL_MAX_N);
-  return hipFuncSetAttribute((const void*)k_finalize, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             want < max_lds ? want : max_lds);
 }
 
 }  // namespace pwl

@@ -37,30 +37,52 @@ __device__ inline double sampled_second(const FuncDesc& f, double x) {
   return (1.0 - u) * f.sf2[i] + u * f.sf2[i + 1];
 }
 
-__device__ inline float f_value32(const FuncDesc& f, float x) {
-  switch (f.func) {
-    case PWL_F_GAUSSIAN: {
-      const float s = f.p32[0], amp = f.p32[1];
-      return amp * expf(-(x * x) / (2.0f * s * s));
-    }
-    case PWL_F_LORENTZIAN: {
-      const float u = x / f.p32[0];
-      return f.p32[1] / fmaf(u, u, 1.0f);
-    }
-    case PWL_F_BESSEL_J0:
-      return f.p32[0] * j0f(x);
-    case PWL_F_POLY: {
-      float r = f.p32[PWL_MAX_PARAMS - 1];
-      for (int k = PWL_MAX_PARAMS - 2; k >= 0; --k) r = fmaf(r, x, f.p32[k]);
-      return r;
-    }
-    case PWL_F_EXP:
-      return f.p32[1] * expf(f.p32[0] * x);
-    case PWL_F_SAMPLED:
-      return (float)sampled_value(f, (double)x);
-    default:
-      return __builtin_nanf("");
+// f(x) for a function known at compile time, in FP32.
+template <int FUNC>
+__device__ inline float f_value32_of(const FuncDesc& f, float x) {
+  if constexpr (FUNC == PWL_F_GAUSSIAN) {
+    const float s = f.p32[0], amp = f.p32[1];
+    return amp * expf(-(x * x) / (2.0f * s * s));
+  } else if constexpr (FUNC == PWL_F_LORENTZIAN) {
+    const float u = x / f.p32[0];
+    return f.p32[1] / fmaf(u, u, 1.0f);
+  } else if constexpr (FUNC == PWL_F_BESSEL_J0) {
+    return f.p32[0] * j0f(x);
+  } else if constexpr (FUNC == PWL_F_POLY) {
+    float r = f.p32[PWL_MAX_PARAMS - 1];
+    for (int k = PWL_MAX_PARAMS - 2; k >= 0; --k) r = fmaf(r, x, f.p32[k]);
+    return r;
+  } else if constexpr (FUNC == PWL_F_EXP) {
+    return f.p32[1] * expf(f.p32[0] * x);
+  } else {
+    static_assert(FUNC == PWL_F_SAMPLED, "unknown function");
+    return (float)sampled_value(f, (double)x);
   }
+}
+
+// Calls body(FuncTag) for the function f describes, so that a loop over
+// points branches on the function once.
+template <int FUNC>
+struct FuncTag {
+  static constexpr int value = FUNC;
+};
+template <class Body>
+__device__ inline void with_func(const FuncDesc& f, const Body& body) {
+  switch (f.func) {
+    case PWL_F_GAUSSIAN: body(FuncTag<PWL_F_GAUSSIAN>{}); break;
+    case PWL_F_LORENTZIAN: body(FuncTag<PWL_F_LORENTZIAN>{}); break;
+    case PWL_F_BESSEL_J0: body(FuncTag<PWL_F_BESSEL_J0>{}); break;
+    case PWL_F_POLY: body(FuncTag<PWL_F_POLY>{}); break;
+    case PWL_F_EXP: body(FuncTag<PWL_F_EXP>{}); break;
+    case PWL_F_SAMPLED: body(FuncTag<PWL_F_SAMPLED>{}); break;
+    default: break;
+  }
+}
+
+__device__ inline float f_value32(const FuncDesc& f, float x) {
+  float y = __builtin_nanf("");
+  with_func(f, [&](auto func) { y = f_value32_of<decltype(func)::value>(f, x); });
+  return y;
 }
 
 // f''(x) in FP64, from calculus.

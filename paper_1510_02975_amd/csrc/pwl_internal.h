@@ -118,11 +118,6 @@ inline size_t eval_lds_bytes_pairs(int N, int K) {
   return 16 * (size_t)(image_pair_words(N) + image_knot_words(N) + image_map_words(K));
 }
 
-// Table finalize: 4 FP64 PCR rows, the FP32 knots and their u16 map cells.
-inline size_t finalize_lds_bytes(int N) {
-  return (4 * sizeof(double) + sizeof(float) + sizeof(uint16_t)) * (size_t)(N + 1);
-}
-
 // Number of map cells for a table of N segments: two per segment on a uniform
 // partition (each cell then holds at most one knot), four on the optimal one.
 // Index-map cells: 2N for a uniform partition, 4N for the optimal one or 8N

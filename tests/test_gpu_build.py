@@ -172,3 +172,26 @@ def test_map_size_per_table(case):
         y_bs = P.pwl_eval(t, x)
     assert torch.equal(y, y_bs)
     t.free()
+
+
+@pytest.mark.parametrize("N", [1, 2, 63, 64, 65, 123, 124, 125, 247, 248, 249, 1023, 1025, 4095, 4096])
+def test_projection_across_workgroup_rows(N):
+    """The projection's rows are solved 124 to a workgroup from a window of
+    rows around them: values at every N around that size, both partitions,
+    against the oracle's tridiagonal solve on the GPU's own knots, and the
+    table evaluated at its knots and between them."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    for func, p, a, b in ((O.GAUSSIAN, (0.7, 1.0), -5.0, 5.0), (O.BESSEL_J0, (1.0,), 0.0, 50.0)):
+        for part in (O.UNIFORM, O.OPTIMAL):
+            t = P.pwl_build(func, p, a, b, N, part, O.PROJ)
+            d = P.pwl_table_download(t)
+            X = d["knots"].astype(np.float64)
+            ref = O.proj_values(func, p, X)
+            assert np.max(np.abs(d["values64"] - ref)) <= VALUE_TOL * fmax_abs(func, p, a, b), (func, part)
+            x = np.concatenate([X[:-1] + (X[1:] - X[:-1]) * f for f in (0.0, 0.3, 0.9)] + [X[-1:]]).astype(np.float32)
+            y = P.pwl_eval(t, torch.from_numpy(x).to(dev)).cpu().numpy()
+            yr = O.evaluate(X, d["values"].astype(np.float64), x.astype(np.float64))
+            assert np.max(np.abs(y - yr)) <= 2e-6 * fmax_abs(func, p, a, b)
+            t.free()
