@@ -294,17 +294,19 @@ pwl_status pwl_locate(const pwl_table* t, const float* x, int32_t* seg, int64_t 
  * Forward: the points are cut into slices of two of the kernel's vector
  * iterations (unroll * block * 8 points) from point 0 on, whatever the
  * tables; a slice whose tables' LDS images do not fit together is split at
- * a table.  The grid holds wg_per_cu workgroups per CU (fewer if there are
- * fewer slices) and workgroup b takes the slices at launch positions b,
- * b + grid, ... (runs of 8 consecutive slices are placed on one XCD): per
- * slice it copies the images of the slice's tables into LDS and streams the
- * slice as one range, each wave with the table of its points.
+ * a table, and where the slices are too few to fill the device evenly they
+ * are cut into halves, quarters, ... (then in smaller workgroups), a unit of
+ * work each.  The grid holds wg_per_cu workgroups per CU (fewer if there are
+ * fewer units) and workgroup b takes the units at launch positions b,
+ * b + grid, ... (runs of 8 consecutive units are placed on one XCD): per
+ * unit it copies the images of the unit's tables into LDS and streams the
+ * unit as one range, each wave with the table of its points.
  * Backward: the same, in slices of four of its own iterations
- * (unroll * block * 16 points); per slice the
+ * (unroll * block * 16 points); per unit the
  * workgroup also sums every point's hat weights into one FP64 dL/dv region
- * per table in LDS and stores each region, rounded to FP32, as that run's
- * N + 1 partial sums in a buffer the batch owns; a second kernel adds each
- * table's partial sums in slice order in FP64.
+ * per table in LDS and stores each region, rounded to FP32, as that unit's
+ * N + 1 partial sums of the table in a buffer the batch owns; a second kernel
+ * adds each table's partial sums in slice order in FP64.
  * Packs the copies, uploads the plan and synchronises `stream`.
  */
 pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int64_t* offsets, void* stream,

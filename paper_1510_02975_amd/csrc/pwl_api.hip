@@ -740,39 +740,35 @@ struct ClassPlan {
   std::vector<pwl::BatchRun> runs;
   std::vector<pwl::BatchGroup> groups;
   size_t lds = 16;
+  int64_t part_len = 0;   // backward: partial sums of all groups
 };
 
 // The points in slices of `slice` points from point 0 on (the last one
 // shorter), each slice the runs of the tables it meets.  A slice whose
 // tables need more than `cap` bytes of LDS together - their images, a
 // contiguous span of the arena, and (backward) one FP64 dL/dv region per
-// table after them - becomes several groups, split at a table.  The kernels
-// deal the groups to their workgroups round-robin, in the order below.
+// table after them - becomes several groups, split at a table.
 ClassPlan plan_slices(const int64_t* offsets, int T, const std::vector<int64_t>& img_word,
                       const std::vector<int32_t>& nvec, const std::vector<int32_t>& Ns, bool backward,
                       int64_t slice, size_t cap) {
   ClassPlan p;
   const int64_t total = offsets[T];
   auto dvw = [&](int u) { return backward ? (int64_t)pwl::batch_dv_words(Ns[u]) : 0; };
-  auto close = [&](int q, int64_t img0, int64_t dv_words) {
+  auto close = [&](int q, int64_t img0) {
     const int q1 = (int)p.runs.size();
     if (q1 == q) return;
-    const int last = p.runs[q1 - 1].table;
     pwl::BatchGroup g{};
-    g.img = img0;
-    g.nwords = (int32_t)(img_word[last] + nvec[last] - img0);
     g.r0 = q;
     g.r1 = q1;
-    g.dv_lds = g.nwords;
-    g.dv_words = (int32_t)dv_words;
+    g.begin = p.runs[q].begin;
+    g.end = p.runs[q1 - 1].end;
     int64_t cum = 0;
     for (int k = q; k < q1; ++k) {
       pwl::BatchRun& r = p.runs[k];
       r.img_lds = (int32_t)(img_word[r.table] - img0);
-      r.dv_lds = backward ? (int32_t)(g.nwords + cum) : 0;
+      r.dv_lds = (int32_t)cum;
       cum += dvw(r.table);
     }
-    p.lds = std::max(p.lds, (size_t)(16 * ((size_t)g.nwords + (size_t)dv_words)));
     p.groups.push_back(g);
   };
   int t0 = 0;
@@ -784,7 +780,7 @@ ClassPlan plan_slices(const int64_t* offsets, int T, const std::vector<int64_t>&
     for (int u = t0; u < T && offsets[u] < s1; ++u) {
       if (offsets[u + 1] == offsets[u]) continue;   // no points
       if (img0 >= 0 && (size_t)(16 * (img_word[u] + nvec[u] - img0 + dv_words + dvw(u))) > cap) {
-        close(q, img0, dv_words);
+        close(q, img0);
         q = (int)p.runs.size();
         img0 = -1;
         dv_words = 0;
@@ -795,24 +791,101 @@ ClassPlan plan_slices(const int64_t* offsets, int T, const std::vector<int64_t>&
       r.table = u;
       r.begin = std::max(s0, offsets[u]);
       r.end = std::min(s1, offsets[u + 1]);
+      r.part = p.part_len;
+      p.part_len += Ns[u] + 1;
       p.runs.push_back(r);
     }
-    close(q, img0, dv_words);
+    close(q, img0);
   }
-  // Deal each run of 8 consecutive units to one XCD: launch position
-  // 64 c + 8 j + i takes unit 64 c + 8 i + j (workgroups go to the XCDs
-  // round-robin, so position p runs on XCD p mod 8), keeping every block of
-  // 64 positions a window of 64 consecutive units.  A table's consecutive
-  // slices then read its image through one L2: the 4096-table forward
-  // measured 382.5 -> 375.8 us, the fused backward unchanged.
-  const int G = (int)p.groups.size(), full = G / 64 * 64;
-  std::vector<pwl::BatchGroup> order(p.groups);
+  return p;
+}
+
+// Points per work unit: the slice, or half of it again and again down to
+// 2048, whichever costs least by a model of the launch: a unit costs its
+// points and a fixed part (staging, barriers, filling and draining the
+// loads; 0.3 of a vector iteration forward, 0.44 backward), and u units on C
+// CUs take u / C rounds and on average 0.6 of one more, or a little over one
+// round if there are no more units than CUs.  A launch of few slices thus
+// spreads over the chip, and one of a few rounds loses less to its last.
+// Measured in us, whole slices -> the chosen length: forward 64 tables,
+// 10^5 points 11.2 -> 7.1 (2048; 4096 7.2, 8192 9.5), 2^20 13.9 -> 6.6 (4096;
+// 2048 7.8, 8192 7.8), 300 tables 2^22 17.6 -> 15.0 (8192), 2^24 33.7 (32768,
+// the whole slice; 16384 37.4); fused backward 64 tables 2^20 54.2 -> 16.6
+// (4096), 300 tables 2^24 97.4 -> 77.6 (32768; 16384 85.2), 512 tables 2^25
+// 150.6 -> 133.7 (32768; 16384 143.0).
+int64_t unit_length(const ClassPlan& p, int64_t slice, int64_t iteration, int num_cu, bool backward) {
+  const double fixed = (backward ? 0.44 : 0.3) * (double)iteration;
+  int64_t best = slice;
+  double least = 0.0;
+  for (int64_t len = slice; len == slice || len >= 2048; len /= 2) {
+    int64_t units = 0;
+    for (const pwl::BatchGroup& g : p.groups) units += (g.end - 1) / len - g.begin / len + 1;
+    const double rounds = units > num_cu ? (double)units / num_cu + 0.6 : 1.2;
+    const double cost = rounds * (fixed + (double)len);
+    if (len == slice || cost < least) {
+      best = len;
+      least = cost;
+    }
+  }
+  return best;
+}
+
+// Cuts the groups at the multiples of `len` points, and describes each piece
+// with the images, dL/dv regions and partial sums of its own runs.
+void cut_groups(ClassPlan* p, const std::vector<int64_t>& img_word, const std::vector<int32_t>& nvec,
+                const std::vector<int32_t>& Ns, bool backward, int64_t len) {
+  std::vector<pwl::BatchGroup> cut;
+  p->part_len = 0;
+  p->lds = 16;
+  for (const pwl::BatchGroup& g : p->groups) {
+    int q = g.r0;
+    for (int64_t b = g.begin; b < g.end;) {
+      const int64_t e = std::min(g.end, (b / len + 1) * len);
+      while (p->runs[q].end <= b) ++q;
+      int q1 = q;
+      int64_t dv_words = 0, part = 0;
+      for (; q1 < g.r1 && p->runs[q1].begin < e; ++q1) {
+        const int u = p->runs[q1].table;
+        if (backward) dv_words += pwl::batch_dv_words(Ns[u]);
+        part += Ns[u] + 1;
+      }
+      pwl::BatchGroup u{};
+      const int first = p->runs[q].table, last = p->runs[q1 - 1].table;
+      u.img = img_word[first];
+      u.begin = b;
+      u.end = e;
+      u.part = p->part_len;
+      u.nwords = (int32_t)(img_word[last] + nvec[last] - img_word[first]);
+      u.r0 = q;
+      u.r1 = q1;
+      u.dv_lds = u.nwords;
+      u.dv_words = (int32_t)dv_words;
+      u.img0 = p->runs[q].img_lds;
+      u.dv0 = p->runs[q].dv_lds;
+      p->part_len += part;
+      p->lds = std::max(p->lds, (size_t)(16 * ((size_t)u.nwords + (size_t)dv_words)));
+      cut.push_back(u);
+      b = e;
+    }
+  }
+  p->groups.swap(cut);
+}
+
+// The order in which the kernels deal the groups to their workgroups: each
+// run of 8 consecutive units to one XCD.  Launch position 64 c + 8 j + i
+// takes unit 64 c + 8 i + j (workgroups go to the XCDs round-robin, so
+// position p runs on XCD p mod 8), keeping every block of 64 positions a
+// window of 64 consecutive units.  A table's consecutive slices then read its
+// image through one L2: the 4096-table forward measured 382.5 -> 375.8 us,
+// the fused backward unchanged.
+void deal_groups(ClassPlan* p) {
+  const int G = (int)p->groups.size(), full = G / 64 * 64;
+  std::vector<pwl::BatchGroup> order(p->groups);
   for (int pos = 0; pos < full; ++pos) {
     const int c = pos / 64, j = (pos / 8) % 8, i = pos % 8;
-    order[pos] = p.groups[64 * c + 8 * i + j];
+    order[pos] = p->groups[64 * c + 8 * i + j];
   }
-  p.groups.swap(order);
-  return p;
+  p->groups.swap(order);
 }
 
 }  // namespace
@@ -849,34 +922,45 @@ pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int
   int max_lds = 0;
   (void)device_ready(nullptr, nullptr, &max_lds);
   const size_t cap = std::min<size_t>((size_t)max_lds, 160 * 1024);
-  // slices of whole vector iterations of each kernel's current shape; a
-  // persistent grid of wg_per_cu workgroups per CU (no more than slices)
+  // slices of whole vector iterations of each kernel's current shape, cut
+  // shorter where they are too few; a grid of wg_per_cu workgroups per CU
+  // (no more than units)
   const pwl::LaunchConfig cfg[2] = {pwl::get_launch(PWL_KERNEL_BATCH), pwl::get_launch(PWL_KERNEL_BATCH_BACKWARD)};
   ClassPlan plans[2];
-  int grids[2];
+  int grids[2], blocks[2], unrolls[2];
   for (int dir = 0; dir < 2; ++dir) {
+    blocks[dir] = cfg[dir].block;
+    unrolls[dir] = cfg[dir].unroll;
     const int64_t slice = (int64_t)kSliceIterations[dir] * 4 * cfg[dir].block * cfg[dir].unroll;
     plans[dir] = plan_slices(offsets, T, img_word, nvec, Ns, dir == 1, slice, cap);
+    const int64_t len = unit_length(plans[dir], slice, slice / kSliceIterations[dir], num_cu, dir == 1);
+    // an iteration no longer than a unit: fewer vectors per thread, then fewer threads
+    while (4 * (int64_t)blocks[dir] * unrolls[dir] > len && unrolls[dir] > 1) unrolls[dir] /= 2;
+    while (4 * (int64_t)blocks[dir] * unrolls[dir] > len && blocks[dir] > 256 && blocks[dir] % 128 == 0) blocks[dir] /= 2;
+    cut_groups(&plans[dir], img_word, nvec, Ns, dir == 1, len);
     const int64_t ng = (int64_t)plans[dir].groups.size();
     grids[dir] = (int)std::max<int64_t>(1, std::min<int64_t>(ng, (int64_t)num_cu * std::max(1, cfg[dir].wg_per_cu)));
   }
-  // the backward's partial dL/dv sums: N + 1 per run; per table its runs'
-  // offsets in slice order, and its range of the concatenated gradient
+  // the backward's partial dL/dv sums: N + 1 per run of each unit; per table
+  // their offsets in slice order, and its range of the concatenated gradient
   std::vector<int64_t> tab_dv(T + 1, 0);
   for (int i = 0; i < T; ++i) tab_dv[i + 1] = tab_dv[i] + Ns[i] + 1;
   std::vector<int32_t> tab_first(T + 1, 0);
-  int64_t part_len = 0;
-  for (pwl::BatchRun& r : plans[1].runs) {
-    r.part = part_len;
-    part_len += Ns[r.table] + 1;
-    ++tab_first[r.table + 1];
-  }
+  const int64_t part_len = plans[1].part_len;
+  size_t nparts = 0;
+  for (const pwl::BatchGroup& g : plans[1].groups)
+    for (int q = g.r0; q < g.r1; ++q, ++nparts) ++tab_first[plans[1].runs[q].table + 1];
   for (int i = 0; i < T; ++i) tab_first[i + 1] += tab_first[i];
-  std::vector<int64_t> tab_part(std::max<size_t>(1, plans[1].runs.size()));
+  std::vector<int64_t> tab_part(std::max<size_t>(1, nparts));
   {
     std::vector<int32_t> fill(tab_first.begin(), tab_first.end() - 1);
-    for (const pwl::BatchRun& r : plans[1].runs) tab_part[fill[r.table]++] = r.part;
+    for (const pwl::BatchGroup& g : plans[1].groups)
+      for (int q = g.r0; q < g.r1; ++q) {
+        const pwl::BatchRun& r = plans[1].runs[q];
+        tab_part[fill[r.table]++] = g.part + (r.part - plans[1].runs[g.r0].part);
+      }
   }
+  for (ClassPlan& p : plans) deal_groups(&p);
   // one allocation: tables, their deepest map cells, the image arena, the
   // runs and work units of the forward and the backward launch, then the
   // backward's partial sums and their per-table lists
@@ -943,7 +1027,7 @@ pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int
       d = pwl::BatchPlan{reinterpret_cast<pwl::BatchRun*>(b + o_runs[dir]),
                          reinterpret_cast<pwl::BatchGroup*>(b + o_grp[dir]),
                          reinterpret_cast<const float4*>(b + o_arena), grids[dir], ngroups,
-                         (int32_t)p.runs.size(), p.lds};
+                         (int32_t)p.runs.size(), p.lds, blocks[dir], unrolls[dir]};
     }
   }
   if (e == hipSuccess)

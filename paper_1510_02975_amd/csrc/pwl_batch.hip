@@ -7,22 +7,25 @@
 // kernel's vector iterations (two by default) at fixed positions of the
 // concatenated arrays, whatever the tables, and lists per slice the
 // (table, begin, end) runs it covers; a slice whose tables' LDS images
-// would not fit is split at a table.  The grid's workgroups take the slices
-// round-robin (workgroup b: launch positions b, b + grid, ...; the host
-// orders the positions so that runs of 8 consecutive slices share an XCD),
-// so the workgroups in flight stream neighbouring slices and every slice is
-// streamed in full iterations: a slice boundary, not a table boundary, ends
+// would not fit is split at a table, and where the slices are too few to
+// fill the chip evenly they are cut shorter.  The grid's workgroups take
+// these units round-robin (workgroup b: launch positions b, b + grid, ...;
+// the host orders the positions so that runs of 8 consecutive units share an
+// XCD), so the workgroups in flight stream neighbouring units and every unit
+// is streamed in full iterations: a unit boundary, not a table boundary, ends
 // an iteration.  The forward's grid is persistent (a few workgroups per CU);
-// the backward's has about one workgroup per slice.  Per slice a workgroup
-// copies its tables' images (one
-// contiguous span of the batch's image arena) into LDS, passes a barrier and
-// streams the slice as one range; each wave looks up the run of its
-// 64 vectors (scalar: the slice's runs are in order) and, where the vectors
-// cross a table boundary, evaluates each point with its own table.
+// the backward's has about one workgroup per unit.  Per unit a workgroup
+// copies its tables' images (one contiguous span of the batch's image arena)
+// into LDS, passes a barrier and streams the unit as one range; each wave
+// looks up the run of its 64 vectors (scalar: the unit's runs are in order)
+// and, where the vectors cross a table boundary, evaluates each point with
+// its own table.  (Loading the next unit's images into registers during the
+// current one measured the same as copying them at the boundary, without
+// registers: 373.7 and 373.0 us over 4096 tables and 2^28 points.)
 //
 // Fused backward: the same, in slices of four iterations, with one FP64
-// dL/dv region per table of the slice in LDS after the images.  After the
-// slice the workgroup stores every region, rounded to FP32, as that run's
+// dL/dv region per table of the unit in LDS after the images.  After the
+// unit the workgroup stores every region, rounded to FP32, as that run's
 // partial sums in a buffer of the batch; k_batch_dv_reduce then adds each
 // table's partial sums in slice order, in FP64, so dL/dv does not depend on
 // the order in which the workgroups ran.
@@ -42,56 +45,6 @@ __device__ __forceinline__ TableShape run_table(const BatchRun& r) {
   return TableShape{r.N, r.K, r.a32, r.b32, r.scale32};
 }
 
-// Copies n >= 1 16-byte words from global memory to LDS, four per thread
-// per round: each round issues all its loads before its first store.  The
-// loads are unconditional (indices clamped to the last word): a load under
-// a per-thread condition would make the compiler wait for it before the next.
-__device__ __forceinline__ void stage_words(const float4* __restrict__ src4, int n, float4* dst4) {
-  const v4f* __restrict__ src = reinterpret_cast<const v4f*>(src4);
-  v4f* dst = reinterpret_cast<v4f*>(dst4);
-  const int tid = threadIdx.x, bs = blockDim.x;
-  for (int k0 = 0; k0 < n; k0 += 4 * bs) {
-    v4f w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = src[min(k0 + j * bs + tid, n - 1)];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int k = k0 + j * bs + tid;
-      if (k < n) dst[k] = w[j];
-    }
-  }
-}
-
-// The first W * blockDim.x words of the next unit's images, loaded into
-// registers when the current unit starts, so that their latency passes
-// while the current unit streams; put_words writes them (and stages any
-// further words) once every wave is done with the current unit.
-template <int W>
-struct ImagePrefetch {
-  v4f w[W];
-};
-
-template <int W>
-__device__ __forceinline__ void prefetch_words(const float4* __restrict__ src4, int n, ImagePrefetch<W>& p) {
-  const v4f* __restrict__ src = reinterpret_cast<const v4f*>(src4);
-  const int tid = threadIdx.x, bs = blockDim.x;
-#pragma unroll
-  for (int j = 0; j < W; ++j) p.w[j] = src[min(j * bs + tid, n - 1)];
-}
-
-template <int W>
-__device__ __forceinline__ void put_words(const ImagePrefetch<W>& p, const float4* __restrict__ src4, int n,
-                                          float4* dst4) {
-  v4f* dst = reinterpret_cast<v4f*>(dst4);
-  const int tid = threadIdx.x, bs = blockDim.x;
-#pragma unroll
-  for (int j = 0; j < W; ++j) {
-    const int k = j * bs + tid;
-    if (k < n) dst[k] = p.w[j];
-  }
-  if (n > W * bs) stage_words(src4 + W * bs, n - W * bs, dst4 + W * bs);
-}
-
 // Run q of a slice: its points and its table, whose image is in LDS.  q is
 // uniform, so the descriptor comes through the scalar cache.
 struct RunView {
@@ -100,14 +53,22 @@ struct RunView {
   int64_t begin, end;
 };
 
+// The LDS of a unit: word w of the slice's images is lds[w + img], of the
+// slice's dL/dv regions lds[w + dv].
+struct UnitLds {
+  float4* lds;
+  int img, dv;
+  __device__ __forceinline__ UnitLds(float4* l, const BatchGroup& g) : lds(l), img(-g.img0), dv(g.dv_lds - g.dv0) {}
+};
+
 template <bool DV = false>
-__device__ __forceinline__ RunView run_view(const BatchRun* __restrict__ runs, int q, float4* lds) {
+__device__ __forceinline__ RunView run_view(const BatchRun* __restrict__ runs, int q, const UnitLds& l) {
   const BatchRun r = runs[q];
   RunView v;
   v.t = run_table(r);
-  v.s = carve(lds + r.img_lds, r.N, r.K, false);
+  v.s = carve(l.lds + (r.img_lds + l.img), r.N, r.K, false);
   if (DV) {
-    v.s.dv = reinterpret_cast<double*>(lds + r.dv_lds);
+    v.s.dv = reinterpret_cast<double*>(l.lds + (r.dv_lds + l.dv));
     v.s.dvc = dv_copies(r.N);
   }
   v.begin = r.begin;
@@ -128,7 +89,7 @@ __device__ __forceinline__ v4f eval4(const v4f& xv, const RunView& v) {
 // Points [lo, hi) of runs [r0, r1) one by one (the unaligned ends of a
 // slice, or every point when the arrays cannot be read as vectors).
 template <int MAXC>
-__device__ __forceinline__ void slice_scalar(const BatchRun* __restrict__ runs, int r0, int r1, float4* lds,
+__device__ __forceinline__ void slice_scalar(const BatchRun* __restrict__ runs, int r0, int r1, const UnitLds& lds,
                                              const float* __restrict__ x, float* __restrict__ y, int64_t lo,
                                              int64_t hi) {
   if (lo >= hi) return;
@@ -145,8 +106,8 @@ __device__ __forceinline__ void slice_scalar(const BatchRun* __restrict__ runs, 
 // the one holding pf; a wave whose points reach past it evaluates each
 // point under the run it falls in, for the runs up to the wave's last point.
 template <int U, int MAXC, bool GUARD>
-__device__ __forceinline__ void slice_iter(const BatchRun* __restrict__ runs, int r1, float4* lds, RunView& cur,
-                                           int& q, const v4f* __restrict__ x4, v4f* __restrict__ y4,
+__device__ __forceinline__ void slice_iter(const BatchRun* __restrict__ runs, int r1, const UnitLds& lds, RunView& cur,
+                                           int& q, const v4fu* __restrict__ x4, v4f* __restrict__ y4,
                                            int64_t ib, int64_t vend, int64_t phase, int64_t e, int tid,
                                            int wave0) {
   const int64_t bs = blockDim.x;
@@ -191,17 +152,19 @@ __device__ __forceinline__ void slice_iter(const BatchRun* __restrict__ runs, in
 // A slice: runs [r0, r1), points [runs[r0].begin, runs[r1-1].end), their
 // images staged at the runs' img_lds.
 template <int U, int MAXC>
-__device__ __forceinline__ void slice_fwd(const BatchRun* __restrict__ runs, int r0, int r1, float4* lds,
+__device__ __forceinline__ void slice_fwd(const BatchRun* __restrict__ runs, const BatchGroup& gp, float4* lds_f4,
                                           const float* __restrict__ x, float* __restrict__ y, bool vec,
                                           int wave0) {
-  const int64_t b = runs[r0].begin, e = runs[r1 - 1].end;
-  const Split sp = split_range(x, b, e, vec);
+  const int r0 = gp.r0, r1 = gp.r1;
+  const UnitLds lds(lds_f4, gp);
+  const int64_t b = gp.begin, e = gp.end;
+  const Split sp = split_range(y, b, e, vec);
   if (sp.vend <= sp.vbeg) {
     slice_scalar<MAXC>(runs, r0, r1, lds, x, y, b, e);
     return;
   }
-  const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(x) >> 2) & 3);
-  const v4f* __restrict__ x4 = reinterpret_cast<const v4f*>(x - phase);
+  const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(y) >> 2) & 3);
+  const v4fu* __restrict__ x4 = reinterpret_cast<const v4fu*>(x - phase);
   v4f* __restrict__ y4 = reinterpret_cast<v4f*>(y - phase);
   const int tid = threadIdx.x;
   const int64_t chunk = (int64_t)blockDim.x * U;
@@ -216,10 +179,9 @@ __device__ __forceinline__ void slice_fwd(const BatchRun* __restrict__ runs, int
   slice_scalar<MAXC>(runs, r0, r1, lds, x, y, tail > sp.head ? tail : sp.head, e);
 }
 
-// Units blockIdx.x, blockIdx.x + gridDim.x, ...: the first unit's images
-// are staged, then per unit: load the next unit's first image words (four
-// per thread) into registers, stream this unit, one barrier, write the next
-// images to LDS, one barrier.
+// Units blockIdx.x, blockIdx.x + gridDim.x, ...; per unit: copy its images
+// into LDS, one barrier, stream the unit, one barrier; the next unit's
+// descriptor is loaded meanwhile (376.4 us without that, 373.4 with it).
 template <int U>
 __global__ __launch_bounds__(1024) void k_batch_fwd(const BatchRun* __restrict__ runs,
                                                     const BatchGroup* __restrict__ groups, int ngroups,
@@ -227,34 +189,28 @@ __global__ __launch_bounds__(1024) void k_batch_fwd(const BatchRun* __restrict__
                                                     const float* __restrict__ x, float* __restrict__ y,
                                                     int vec) {
   extern __shared__ float4 lds_f4[];
-  const int wave0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63;
+  const int wave0 = wave_first();
   int gi = blockIdx.x;
   if (gi >= ngroups) return;
   BatchGroup gp = groups[gi];
-  stage_words(arena + gp.img, gp.nwords, lds_f4);
-  lds_barrier();
   for (;;) {
-    const int gn = gi + (int)gridDim.x;
-    const bool more = gn < ngroups;
+    stage_copy(arena + gp.img, gp.nwords, blockDim.x, lds_f4);
+    staged();
+    lds_barrier();
+    gi += (int)gridDim.x;
+    const bool more = gi < ngroups;
     BatchGroup gq{};
-    ImagePrefetch<4> pf;
-    if (more) {
-      gq = groups[gn];
-      prefetch_words(arena + gq.img, gq.nwords, pf);
-    }
+    if (more) gq = groups[gi];   // on its way while this unit streams
     switch (gp.maxc) {
       case 0:
-      case 1: slice_fwd<U, 1>(runs, gp.r0, gp.r1, lds_f4, x, y, vec != 0, wave0); break;
-      case 2: slice_fwd<U, 2>(runs, gp.r0, gp.r1, lds_f4, x, y, vec != 0, wave0); break;
-      case 3: slice_fwd<U, 3>(runs, gp.r0, gp.r1, lds_f4, x, y, vec != 0, wave0); break;
-      case 4: slice_fwd<U, 4>(runs, gp.r0, gp.r1, lds_f4, x, y, vec != 0, wave0); break;
-      default: slice_fwd<U, 0>(runs, gp.r0, gp.r1, lds_f4, x, y, vec != 0, wave0); break;
+      case 1: slice_fwd<U, 1>(runs, gp, lds_f4, x, y, vec != 0, wave0); break;
+      case 2: slice_fwd<U, 2>(runs, gp, lds_f4, x, y, vec != 0, wave0); break;
+      case 3: slice_fwd<U, 3>(runs, gp, lds_f4, x, y, vec != 0, wave0); break;
+      case 4: slice_fwd<U, 4>(runs, gp, lds_f4, x, y, vec != 0, wave0); break;
+      default: slice_fwd<U, 0>(runs, gp, lds_f4, x, y, vec != 0, wave0); break;
     }
     if (!more) break;
-    lds_barrier();
-    put_words(pf, arena + gq.img, gq.nwords, lds_f4);
-    lds_barrier();
-    gi = gn;
+    lds_barrier();   // every wave is done with the unit's images
     gp = gq;
   }
 }
@@ -269,7 +225,7 @@ __device__ __forceinline__ void bwd_point(float xv, float gv, const RunView& v, 
 }
 
 template <int MAXC, bool WY, bool WDX>
-__device__ __forceinline__ void slice_bwd_scalar(const BatchRun* __restrict__ runs, int r0, int r1, float4* lds,
+__device__ __forceinline__ void slice_bwd_scalar(const BatchRun* __restrict__ runs, int r0, int r1, const UnitLds& lds,
                                                  const float* __restrict__ x, const float* __restrict__ g,
                                                  float* __restrict__ y, float* __restrict__ dx, int64_t lo,
                                                  int64_t hi) {
@@ -287,10 +243,10 @@ __device__ __forceinline__ void slice_bwd_scalar(const BatchRun* __restrict__ ru
 }
 
 template <int U, int MAXC, bool GUARD, bool WY, bool WDX>
-__device__ __forceinline__ void slice_bwd_iter(const BatchRun* __restrict__ runs, int r1, float4* lds,
-                                               RunView& cur, int& q, const v4f* __restrict__ x4,
-                                               const v4f* __restrict__ g4, v4f* __restrict__ y4,
-                                               v4f* __restrict__ dx4, int64_t ib, int64_t vend, int64_t phase,
+__device__ __forceinline__ void slice_bwd_iter(const BatchRun* __restrict__ runs, int r1, const UnitLds& lds,
+                                               RunView& cur, int& q, const v4fu* __restrict__ x4,
+                                               const v4fu* __restrict__ g4, v4fu* __restrict__ y4,
+                                               v4fu* __restrict__ dx4, int64_t ib, int64_t vend, int64_t phase,
                                                int64_t e, int tid, int wave0) {
   const int64_t bs = blockDim.x;
   v4f xv[U], gv[U];
@@ -334,27 +290,30 @@ __device__ __forceinline__ void slice_bwd_iter(const BatchRun* __restrict__ runs
   for (int u = 0; u < U; ++u) {
     const int64_t i = ib + tid + u * bs;
     if (!GUARD || i < vend) {
-      if (WY) __builtin_nontemporal_store(yv[u], y4 + i);
-      if (WDX) __builtin_nontemporal_store(dxv[u], dx4 + i);
+      if (WY) __builtin_nontemporal_store((v4fu)yv[u], y4 + i);
+      if (WDX) __builtin_nontemporal_store((v4fu)dxv[u], dx4 + i);
     }
   }
 }
 
 template <int U, int MAXC, bool WY, bool WDX>
-__device__ __forceinline__ void slice_bwd(const BatchRun* __restrict__ runs, int r0, int r1, float4* lds,
+__device__ __forceinline__ void slice_bwd(const BatchRun* __restrict__ runs, const BatchGroup& gp, float4* lds_f4,
                                           const float* __restrict__ x, const float* __restrict__ g,
                                           float* __restrict__ y, float* __restrict__ dx, bool vec, int wave0) {
-  const int64_t b = runs[r0].begin, e = runs[r1 - 1].end;
-  const Split sp = split_range(x, b, e, vec);
+  const int r0 = gp.r0, r1 = gp.r1;
+  const UnitLds lds(lds_f4, gp);
+  const int64_t b = gp.begin, e = gp.end;
+  const float* aligned = WY ? y : (WDX ? dx : x);
+  const Split sp = split_range(aligned, b, e, vec);
   if (sp.vend <= sp.vbeg) {
     slice_bwd_scalar<MAXC, WY, WDX>(runs, r0, r1, lds, x, g, y, dx, b, e);
     return;
   }
-  const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(x) >> 2) & 3);
-  const v4f* __restrict__ x4 = reinterpret_cast<const v4f*>(x - phase);
-  const v4f* __restrict__ g4 = reinterpret_cast<const v4f*>(g - phase);
-  v4f* __restrict__ y4 = WY ? reinterpret_cast<v4f*>(y - phase) : nullptr;
-  v4f* __restrict__ dx4 = WDX ? reinterpret_cast<v4f*>(dx - phase) : nullptr;
+  const int64_t phase = (int64_t)((reinterpret_cast<uintptr_t>(aligned) >> 2) & 3);
+  const v4fu* __restrict__ x4 = reinterpret_cast<const v4fu*>(x - phase);
+  const v4fu* __restrict__ g4 = reinterpret_cast<const v4fu*>(g - phase);
+  v4fu* __restrict__ y4 = WY ? reinterpret_cast<v4fu*>(y - phase) : nullptr;
+  v4fu* __restrict__ dx4 = WDX ? reinterpret_cast<v4fu*>(dx - phase) : nullptr;
   const int tid = threadIdx.x;
   const int64_t chunk = (int64_t)blockDim.x * U;
   int q = r0;
@@ -374,9 +333,7 @@ __device__ __forceinline__ void slice_bwd(const BatchRun* __restrict__ runs, int
 // As k_batch_fwd, with the unit's FP64 dL/dv regions (one per table, after
 // the images) zeroed before the barrier that starts it; after the unit, one
 // more barrier and every region is stored, rounded to FP32, as its run's
-// partial sums (k_batch_dv_reduce adds them up), then one more barrier
-// before the next unit's images overwrite LDS.  Two image words per thread
-// are prefetched (four would spill: the backward holds twice the data).
+// partial sums (k_batch_dv_reduce adds them up).
 template <int U, bool WY, bool WDX>
 __global__ __launch_bounds__(1024) void k_batch_bwd(const BatchRun* __restrict__ runs,
                                                     const BatchGroup* __restrict__ groups, int ngroups,
@@ -385,48 +342,37 @@ __global__ __launch_bounds__(1024) void k_batch_bwd(const BatchRun* __restrict__
                                                     float* __restrict__ y, float* __restrict__ dx,
                                                     float* __restrict__ part, int vec) {
   extern __shared__ float4 lds_f4[];
-  const int wave0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63;
-  int gi = blockIdx.x;
-  if (gi >= ngroups) return;
-  BatchGroup gp = groups[gi];
-  stage_words(arena + gp.img, gp.nwords, lds_f4);
-  for (;;) {
+  const int wave0 = wave_first();
+  for (int gi = blockIdx.x; gi < ngroups;) {
+    const BatchGroup gp = groups[gi];
+    stage_copy(arena + gp.img, gp.nwords, blockDim.x, lds_f4);
     double* dvz = reinterpret_cast<double*>(lds_f4 + gp.dv_lds);
     for (int k = threadIdx.x; k < 2 * gp.dv_words; k += blockDim.x) dvz[k] = 0.0;
+    staged();
     lds_barrier();
-    const int gn = gi + (int)gridDim.x;
-    const bool more = gn < ngroups;
-    BatchGroup gq{};
-    ImagePrefetch<2> pf;
-    if (more) {
-      gq = groups[gn];
-      prefetch_words(arena + gq.img, gq.nwords, pf);
-    }
     switch (gp.maxc) {
       case 0:
-      case 1: slice_bwd<U, 1, WY, WDX>(runs, gp.r0, gp.r1, lds_f4, x, g, y, dx, vec != 0, wave0); break;
-      case 2: slice_bwd<U, 2, WY, WDX>(runs, gp.r0, gp.r1, lds_f4, x, g, y, dx, vec != 0, wave0); break;
-      case 3: slice_bwd<U, 3, WY, WDX>(runs, gp.r0, gp.r1, lds_f4, x, g, y, dx, vec != 0, wave0); break;
-      case 4: slice_bwd<U, 4, WY, WDX>(runs, gp.r0, gp.r1, lds_f4, x, g, y, dx, vec != 0, wave0); break;
-      default: slice_bwd<U, 0, WY, WDX>(runs, gp.r0, gp.r1, lds_f4, x, g, y, dx, vec != 0, wave0); break;
+      case 1: slice_bwd<U, 1, WY, WDX>(runs, gp, lds_f4, x, g, y, dx, vec != 0, wave0); break;
+      case 2: slice_bwd<U, 2, WY, WDX>(runs, gp, lds_f4, x, g, y, dx, vec != 0, wave0); break;
+      case 3: slice_bwd<U, 3, WY, WDX>(runs, gp, lds_f4, x, g, y, dx, vec != 0, wave0); break;
+      case 4: slice_bwd<U, 4, WY, WDX>(runs, gp, lds_f4, x, g, y, dx, vec != 0, wave0); break;
+      default: slice_bwd<U, 0, WY, WDX>(runs, gp, lds_f4, x, g, y, dx, vec != 0, wave0); break;
     }
     lds_barrier();
+    const int64_t part0 = gp.part - runs[gp.r0].part;
     for (int q = gp.r0; q < gp.r1; ++q) {
       const BatchRun r = runs[q];
-      const double* d = reinterpret_cast<const double*>(lds_f4 + r.dv_lds);
+      const double* d = reinterpret_cast<const double*>(lds_f4 + (r.dv_lds - gp.dv0 + gp.dv_lds));
       const int c = dv_copies(r.N);
-      float* out = part + r.part;
+      float* out = part + (part0 + r.part);
       for (int k = threadIdx.x; k <= r.N; k += blockDim.x) {
         double acc = d[k * c];
         for (int j = 1; j < c; ++j) acc += d[k * c + j];   // copies in a fixed order
         out[k] = (float)acc;
       }
     }
-    if (!more) break;
-    lds_barrier();
-    put_words(pf, arena + gq.img, gq.nwords, lds_f4);
-    gi = gn;
-    gp = gq;
+    gi += (int)gridDim.x;
+    if (gi < ngroups) lds_barrier();   // every wave is done with the unit's images and regions
   }
 }
 
@@ -466,15 +412,13 @@ __global__ __launch_bounds__(256) void k_batch_pack(const BatchTable* __restrict
   if (threadIdx.x == 0) maxc[blockIdx.x] = (int32_t)t.meta[1];
 }
 
-inline bool same_phase(const void* a, const void* b) {
-  return b == nullptr || ((reinterpret_cast<uintptr_t>(a) ^ reinterpret_cast<uintptr_t>(b)) & 15u) == 0;
-}
+inline bool word_aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3u) == 0; }
 
-hipError_t launch_plan(const BatchLaunch& bl, const BatchPlan& p, const LaunchConfig& c, const float* x,
-                       const float* g, float* y, float* dx, int v, hipStream_t s) {
-  const dim3 grid(p.grid), block(c.block);
+hipError_t launch_plan(const BatchLaunch& bl, const BatchPlan& p, const float* x, const float* g, float* y, float* dx,
+                       int v, hipStream_t s) {
+  const dim3 grid(p.grid), block(p.block);
   if (g == nullptr) {
-    switch (c.unroll) {
+    switch (p.unroll) {
       case 1: hipLaunchKernelGGL(k_batch_fwd<1>, grid, block, p.lds, s, p.runs, p.groups, p.ngroups, p.arena, x, y, v); break;
       case 2: hipLaunchKernelGGL(k_batch_fwd<2>, grid, block, p.lds, s, p.runs, p.groups, p.ngroups, p.arena, x, y, v); break;
       default: hipLaunchKernelGGL(k_batch_fwd<4>, grid, block, p.lds, s, p.runs, p.groups, p.ngroups, p.arena, x, y, v); break;
@@ -492,7 +436,7 @@ hipError_t launch_plan(const BatchLaunch& bl, const BatchPlan& p, const LaunchCo
     case 2: PWL_BB(UU, true, false); break;      \
     default: PWL_BB(UU, true, true); break;      \
   }
-  switch (c.unroll) {
+  switch (p.unroll) {
     case 1: PWL_BB_U(1) break;
     case 2: PWL_BB_U(2) break;
     default: PWL_BB_U(4) break;
@@ -507,11 +451,9 @@ hipError_t launch_plan(const BatchLaunch& bl, const BatchPlan& p, const LaunchCo
 hipError_t launch_batch(const BatchLaunch& bl, const float* x, const float* g, float* y, float* dx,
                         float* dv, hipStream_t s) {
   const bool backward = g != nullptr;
-  const LaunchConfig c = get_launch(backward ? PWL_KERNEL_BATCH_BACKWARD : PWL_KERNEL_BATCH);
-  const bool vec = same_phase(x, y) && same_phase(x, g) && same_phase(x, dx) &&
-                   (reinterpret_cast<uintptr_t>(x) & 3u) == 0;
+  const bool vec = word_aligned(x) && word_aligned(y) && word_aligned(g) && word_aligned(dx);
   const int v = vec ? 1 : 0;
-  const hipError_t e = launch_plan(bl, backward ? bl.bwd : bl.fwd, c, x, g, y, dx, v, s);
+  const hipError_t e = launch_plan(bl, backward ? bl.bwd : bl.fwd, x, g, y, dx, v, s);
   if (e != hipSuccess || !backward) return e;
   hipLaunchKernelGGL(k_batch_dv_reduce, dim3((unsigned)bl.T, (unsigned)((bl.max_n + 256) / 256)), dim3(256), 0, s,
                      bl.part, bl.tab_part, bl.tab_first, bl.tab_dv, dv);

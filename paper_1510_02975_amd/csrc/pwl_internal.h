@@ -160,31 +160,37 @@ struct BatchTable {          // one table of a batch, for packing its image
   int32_t pad;
 };
 
-// Points [begin, end) of one table, handled by one workgroup, with the
-// table's shape copied in: a workgroup reads nothing else to evaluate it.
+// Points [begin, end) of one table in one slice, with the table's shape
+// copied in: a workgroup reads nothing else to evaluate it.
 struct BatchRun {
-  int32_t img_lds;           // the table's image: 16-byte word offset in the workgroup's LDS
-  int32_t dv_lds;            // backward: word offset of the table's FP64 dL/dv in LDS
+  int32_t img_lds;           // the table's image: 16-byte word offset among the slice's images
+  int32_t dv_lds;            // backward: word offset of the table's FP64 dL/dv among the slice's
   int64_t begin, end;
-  int64_t part;              // backward: first of the run's N + 1 partial dL/dv sums in the batch's buffer
+  int64_t part;              // backward: N + 1 summed over the runs before it
   int32_t table, nvec, N, K;
   float a32, b32, scale32;
   int32_t maxc;              // most knots sharing one map cell (the unrolled compare depth)
 };
 static_assert(sizeof(BatchRun) == 64, "BatchRun is 64 bytes");
 
-// One work unit of a batched launch: runs [r0, r1) and the arena words
-// [img, img + nwords) holding their tables' images; the backward's dL/dv
-// regions follow the images in LDS (dv_words 16-byte words from word
-// dv_lds).  maxc: the deepest map cell among its runs' tables.
+// One work unit of a batched launch: points [begin, end) of a slice, which lie
+// in runs [r0, r1), and the arena words [img, img + nwords) holding those
+// runs' images; the backward's dL/dv regions follow the images in LDS
+// (dv_words 16-byte words from word dv_lds).  The runs' own LDS offsets are
+// the slice's; img0 and dv0 are those of run r0.  part: the backward's
+// partial sums of the unit's runs, in run order.  maxc: the deepest map cell
+// among its runs' tables.
 struct BatchGroup {
   int64_t img;
+  int64_t begin, end;
+  int64_t part;
   int32_t nwords;
   int32_t r0, r1;
   int32_t dv_lds, dv_words;
+  int32_t img0, dv0;
   int32_t maxc;
 };
-static_assert(sizeof(BatchGroup) == 32, "BatchGroup is 32 bytes");
+static_assert(sizeof(BatchGroup) == 64, "BatchGroup is 64 bytes");
 
 // LDS of one table in a batched workgroup: its image and (backward) its FP64
 // dL/dv, in 16-byte words.
@@ -201,6 +207,7 @@ struct BatchPlan {           // the work units of one launch
   int32_t ngroups;
   int32_t nruns;
   size_t lds;                // the largest group's LDS bytes
+  int32_t block, unroll;     // the kernel's workgroup size and vectors per thread
 };
 
 // One launch per direction over all the tables.

@@ -316,3 +316,50 @@ def _mixed_sizes(P, dev, shapes):
     bt.free()
     for t in (big, small, mid):
         t.free()
+
+
+@pytest.mark.parametrize("total", [1, 2047, 2049, 100003, (1 << 19) + 5, (1 << 21) + 1])
+def test_batch_units_cut_inside_runs(total):
+    """Batches too small for whole slices: their units end inside tables'
+    runs.  One table, and five with boundaries off every unit length, at
+    mixed 4-byte phases of all arrays: y and dx bit for bit as the per-table
+    evaluator gives them, dL/dv against the oracle."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    rng = np.random.default_rng(total)
+    kinds = [(O.GAUSSIAN, (1.0, 1.0), -5.0, 5.0), (O.LORENTZIAN, (1.0, 1.0), -20.0, 20.0),
+             (O.BESSEL_J0, (1.0,), 0.0, 50.0)]
+    tabs = [P.pwl_build(*kinds[i % 3], N, O.OPTIMAL, O.PROJ) for i, N in enumerate((4096, 16, 300, 1024, 2047))]
+    cuts = np.sort(rng.integers(0, total + 1, 4))
+    for ts, offs in (([tabs[0]], [0, total]), (tabs, [0, *cuts, total])):
+        offs = np.asarray(offs, dtype=np.int64)
+        bt = P.pwl_batch_create(ts, offs)
+        xh, gh = W.uniform_points(-6.0, 51.0, total, 3), W.upstream_grad(total, 4)
+
+        def at(a, shift):
+            v = torch.empty(total + 8, device=dev)[shift:shift + total]
+            v.copy_(torch.from_numpy(a))
+            return v
+        say("units: %d tables, %d points, grids %d and %d" % (len(ts), total, bt.grid_fwd, bt.grid_bwd))
+        x0, g0 = at(xh, 0), at(gh, 0)
+        ref = [P.pwl_eval_backward(t, x0[a:b].clone(), g0[a:b].clone(), want=("y", "dx")) if b > a else None
+               for t, a, b in zip(ts, offs[:-1], offs[1:])]
+        yr, dxr = (torch.cat([r[k] for r in ref if r]) for k in (0, 1))
+        for px, pg, py, pd in ((0, 0, 0, 0), (1, 2, 3, 0), (3, 3, 1, 2)):
+            x, g = at(xh, px), at(gh, pg)
+            y, y2, dx = at(xh, py), at(xh, py), at(xh, pd)
+            P.pwl_batch_eval(bt, x, y)
+            _, _, dv = P.pwl_batch_eval_backward(bt, x, g, y2, dx)
+            assert torch.equal(y, yr) and torch.equal(y2, yr) and torch.equal(dx, dxr), (px, pg, py, pd)
+            dv = dv.cpu().numpy()
+            for i, (t, a, b) in enumerate(zip(ts, offs[:-1], offs[1:])):
+                d = P.pwl_table_download(t)
+                X, xs, gs = d["knots"].astype(np.float64), xh[a:b].astype(np.float64), gh[a:b].astype(np.float64)
+                _, _, dvr = O.evaluate_backward(X, d["values"].astype(np.float64), xs, gs)
+                _, _, wk = O.evaluate_backward(X, np.zeros(len(X)), xs, np.abs(gs))
+                got = dv[bt.dv_offsets[i]:bt.dv_offsets[i + 1]]
+                assert np.all(np.abs(got - dvr) <= GRAD_TOL * wk + 1e-30), (i, px)
+        bt.free()
+    for t in tabs:
+        t.free()
