@@ -15,6 +15,7 @@
 #include "pwl_func.h"
 #include "pwl_internal.h"
 #include "pwl_locate.h"
+#include "pwl_stream.h"
 
 namespace pwl {
 
@@ -60,26 +61,25 @@ __device__ double block_max_scan(double v, double* s_w) {
   return v;
 }
 
-// Inclusive trapezoid sum of the density up to this thread's cell of
-// workgroup `blk`.  Cell j (1-based) spans [t_{j-1}, t_j], t_j = a + j dt,
-// and adds (d_{j-1} + d_j) dt / 2; all threads evaluate the density (one FP64
-// sample each).  (Chains of 32 dependent LDS reads and additions took
-// 2 us longer in each of the two kernels below: N = 1024 7.3 and 11.6 us,
-// 5.0 and 9.7 so.)
-__device__ double scan_block_cells(const BuildParams& bp, int blk, double* s_d, double* s_w) {
+// The density at the corners of workgroup blk's cells, one FP64 sample per
+// thread (s_d, valid after the next barrier).  Cell j (1-based) spans
+// [t_{j-1}, t_j], t_j = a + j dt.
+__device__ void sample_block(const BuildParams& bp, int blk, double* s_d) {
 #pragma clang fp contract(off)
   constexpr int C = kDensityCellsPerBlock;
-  const int tid = threadIdx.x;
   const double dt = (bp.b - bp.a) / (double)bp.M;
-  const double hdt = dt / 2.0;
-  const int j0 = blk * C;
-  for (int s = tid; s <= C; s += kScanThreads) {
-    const int j = j0 + s;
+  for (int s = threadIdx.x; s <= C; s += kScanThreads) {
+    const int j = blk * C + s;
     s_d[s] = (j <= bp.M) ? knot_density(bp.f, bp.a + (double)j * dt) : 0.0;
   }
-  __syncthreads();
-  const double inc = (j0 + tid + 1 <= bp.M) ? (s_d[tid] + s_d[tid + 1]) * hdt : 0.0;
-  return block_scan(inc, s_w);
+}
+
+// This thread's cell's trapezoid, (d_{j-1} + d_j) dt / 2.
+__device__ double block_cell(const BuildParams& bp, int blk, const double* s_d) {
+#pragma clang fp contract(off)
+  const int tid = threadIdx.x;
+  const double hdt = (bp.b - bp.a) / (double)bp.M / 2.0;
+  return (blk * kDensityCellsPerBlock + tid + 1 <= bp.M) ? (s_d[tid] + s_d[tid + 1]) * hdt : 0.0;
 }
 static_assert(kScanThreads == kDensityCellsPerBlock, "one cell per thread");
 static_assert(kMaxDensityBlocks <= kScanThreads, "one block total per thread");
@@ -87,7 +87,9 @@ static_assert(kMaxDensityBlocks <= kScanThreads, "one block total per thread");
 __global__ __launch_bounds__(kScanThreads) void k_density_totals(BuildParams bp, TableDev td) {
   __shared__ double s_d[kDensityCellsPerBlock + 1];
   __shared__ double s_w[kScanWaves];
-  const double sum = scan_block_cells(bp, blockIdx.x, s_d, s_w);
+  sample_block(bp, blockIdx.x, s_d);
+  __syncthreads();
+  const double sum = block_scan(block_cell(bp, blockIdx.x, s_d), s_w);
   if (threadIdx.x == kScanThreads - 1) td.totals[blockIdx.x] = sum;
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     td.status[0] = 0u;
@@ -117,18 +119,22 @@ __global__ __launch_bounds__(kScanThreads) void k_invert_knots(BuildParams bp, T
   constexpr int C = kDensityCellsPerBlock;
   __shared__ double s_d[C + 1];
   __shared__ double s_S[C];
-  __shared__ double s_w[2][kScanWaves];
+  __shared__ double s_w[3][kScanWaves];
   __shared__ double s_off[3];   // offset of this block, offset of the next, S_M
   const int tid = threadIdx.x;
   const int blk = blockIdx.x;
   // Prefix of the workgroup totals, made non-decreasing: the offset of block
   // b + 1 is the end of block b in every workgroup, so each target falls to
   // exactly one of them.
-  const double run = block_max_scan(block_scan(tid < bp.G ? td.totals[tid] : 0.0, s_w[0]), s_w[1]);
+  // (The samples are taken while the totals arrive.)
+  const double tot = tid < bp.G ? td.totals[tid] : 0.0;
+  sample_block(bp, blk, s_d);
+  const double run = block_max_scan(block_scan(tot, s_w[0]), s_w[1]);
   if (tid == 0 && blk == 0) s_off[0] = 0.0;
   if (tid == blk - 1) s_off[0] = run;
   if (tid == blk) s_off[1] = run;
   if (tid == bp.G - 1) s_off[2] = run;
+  s_S[tid] = block_scan(block_cell(bp, blk, s_d), s_w[2]);
   __syncthreads();
   const double off = s_off[0], next = s_off[1], total = s_off[2];
   if (!(total > 0.0) || !isfinite(total)) {
@@ -143,8 +149,6 @@ __global__ __launch_bounds__(kScanThreads) void k_invert_knots(BuildParams bp, T
   // the rounding of the bounds
   const double per = (double)bp.N / total;
   const int i0 = max(1, (int)fmin(off * per, (double)bp.N) - 1), i1 = min(bp.N - 1, (int)fmin(next * per, (double)bp.N) + 1);
-  s_S[tid] = scan_block_cells(bp, blk, s_d, s_w[0]);
-  __syncthreads();
   const double dt = (bp.b - bp.a) / (double)bp.M;
   const double snap = 1e-12 * (bp.b - bp.a);
   for (int i = i0 + tid; i <= i1; i += kScanThreads) {
@@ -185,6 +189,15 @@ constexpr int kSolveHalo = 64;
 constexpr int kFinalizeRows = 124;
 static_assert(kSolveHalo + kFinalizeRows + 1 + kSolveHalo <= kFinalizeThreads, "a row per thread");
 
+// 1 / d for a normal d: the hardware's estimate and two Newton steps, each
+// one exact residual and one correction (last bit aside, the quotient an IEEE
+// division gives, in half the dependent operations).
+__device__ __forceinline__ double reciprocal(double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
+}
+
 // Everything after the knots.  Workgroup g owns rows (knots) and segments
 // [g kFinalizeRows, (g + 1) kFinalizeRows):
 //  1. all knots into LDS: x_k = a + (b - a) k / N for a uniform partition,
@@ -202,9 +215,10 @@ static_assert(kSolveHalo + kFinalizeRows + 1 + kSolveHalo <= kFinalizeThreads, "
 // What bounds it is latency: one workgroup did all of it in 18.5 us at
 // N = 1024 and 50 us at N = 4096 (11 and 13 reduction steps with two barriers
 // each); spread so, with one branch on the function per segment instead of
-// one per node, it takes 10.9 and 17.4 us.
+// one per node and the deepest cell found in passes of independent reads, it
+// takes 9.8 and 10.8 us.
 __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, TableDev td) {
-  __shared__ float X[PWL_MAX_N + 1];                 // FP32 knots
+  __shared__ __align__(16) float X[PWL_MAX_N + 4];   // FP32 knots
   __shared__ double sA[2][kFinalizeThreads], sC[2][kFinalizeThreads], sD[2][kFinalizeThreads],
       sR[2][kFinalizeThreads];                       // the solve's rows, R the reciprocal diagonal
   __shared__ int s_maxc;
@@ -217,16 +231,32 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, T
 
   // 1. knots, collapse, deepest cell
   if (tid == 0) s_maxc = 0;
-  for (int k = tid; k <= N; k += kFinalizeThreads) X[k] = uniform ? (float)uniform_knot(bp, k) : td.knots[k];
+  if (uniform) {
+    for (int k = tid; k <= N; k += kFinalizeThreads) X[k] = (float)uniform_knot(bp, k);
+  } else {
+    stream::stage_copy(td.knots, (N + 4) / 4, kFinalizeThreads, X);   // whole words; the array is padded
+    stream::staged();
+  }
   __syncthreads();
   int bad = 0;
-  for (int k = tid; k < N; k += kFinalizeThreads)
-    if (!(X[k + 1] > X[k])) bad = 1;
+#pragma unroll 4
+  for (int k = tid; k < N; k += kFinalizeThreads) bad |= (X[k + 1] > X[k]) ? 0 : 1;
   const bool collapsed = __syncthreads_or(bad) != 0;
   auto cell = [&](int k) { return map_cell(X[k], bp.a32, bp.scale32, bp.K); };
   if (blockIdx.x == 0) {
-    int run = 0;
-    for (int k = 1 + tid; k < N; k += kFinalizeThreads) {
+    // deeper than r if interior knot k + r shares the cell of knot k, for any
+    // k: a pass per depth of independent reads; past four (the evaluators
+    // take any such depth alike, and it may be thousands) run by run
+    int depth = N >= 2 ? 1 : 0, more = depth;
+    while (more && depth <= kMaxUnrolledCount) {
+      int same = 0;
+#pragma unroll 4
+      for (int k = 1 + tid; k < N - depth; k += kFinalizeThreads) same |= (cell(k) == cell(k + depth)) ? 1 : 0;
+      more = __syncthreads_or(same);
+      if (more) ++depth;
+    }
+    int run = depth;
+    for (int k = 1 + tid; more && k < N; k += kFinalizeThreads) {
       const int u = cell(k);
       if (k > 1 && cell(k - 1) == u) continue;       // not the first interior knot of its cell
       int r = 1;
@@ -274,7 +304,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, T
       c = hr / 6.0;
       d = 2.0 * a + 2.0 * c;
     }
-    sA[0][tid] = a; sC[0][tid] = c; sD[0][tid] = b; sR[0][tid] = 1.0 / d;
+    sA[0][tid] = a; sC[0][tid] = c; sD[0][tid] = b; sR[0][tid] = reciprocal(d);
     __syncthreads();
     // Parallel cyclic reduction: at stride s every row eliminates its
     // couplings to rows i - s and i + s.  No pivoting is needed.  Rows next
@@ -300,7 +330,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_finalize(BuildParams bp, T
       a = an;
       c = cn;
       if (step + 1 < kSolveSteps) {
-        sA[1 - p][tid] = a; sC[1 - p][tid] = c; sD[1 - p][tid] = b; sR[1 - p][tid] = 1.0 / d;
+        sA[1 - p][tid] = a; sC[1 - p][tid] = c; sD[1 - p][tid] = b; sR[1 - p][tid] = reciprocal(d);
         __syncthreads();
       }
     }

@@ -226,9 +226,12 @@ inline bool word_aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p)
 // over the CUs instead, in smaller workgroups with fewer vectors per thread.
 // Forward: one vector per thread up to 1024 per CU, two up to 2048; of 256,
 // 512 and 1024 threads the fewest whose workgroups stage at most 48 KB per
-// CU together (or are alone on it).  Kernel times in us, the tuned shape ->
-// this one: N = 64, 2^20 points 6.2 -> 3.9; N = 1024, 2^14 6.9 -> 3.1, 2^20
-// 7.5 -> 4.7 (256 threads 5.0); N = 4096, 2^20 8.0 -> 5.2 (512 threads 7.0).
+// CU together (or are alone on it; twice that from 4096 vectors per CU).  Kernel times in us, the tuned shape -> this one:
+// N = 64, 2^20 points 6.2 -> 3.9; N = 1024, 2^14 6.9 -> 3.1, 2^20 7.5 -> 4.7
+// (256 threads 5.0); N = 4096, 2^20 8.0 -> 5.2 (512 threads 7.0).  Up to one
+// and a half workgroups per CU, workgroups of fewer threads still fill the
+// last round better where the table is small: 5 * 10^6 points N = 64 11.2 ->
+// 8.8, N = 1024 11.7 -> 10.3 (8 * 10^6 points N = 1024 13.8 -> 15.1).
 // Backward: one vector per thread in 256 threads (512 for N above 1024) up
 // to 512 vectors per CU, then two in 512 threads up to 1024: with the dL/dv
 // reduction N = 64, 2^17 points 8.5 -> 7.0; N = 4096, 2^17 12.6 -> 11.7.
@@ -264,16 +267,18 @@ bool is_small(const LaunchConfig& c, int64_t n4, int num_cu) {
 
 LaunchShape forward_shape(size_t lds, int64_t n4, int64_t n, int num_cu) {
   const LaunchConfig c = g_launch[PWL_KERNEL_FORWARD];
-  if (is_small(c, n4, num_cu)) {
-    const int64_t v = (n4 + num_cu - 1) / num_cu;   // vectors per CU
+  const int64_t v = (n4 + num_cu - 1) / num_cu;   // vectors per CU
+  const bool small = is_small(c, n4, num_cu);
+  if (small || is_small(c, n4 * 2 / 3, num_cu)) {
     const int unroll = v <= 1024 ? 1 : (v <= 2048 ? 2 : 4);
+    const int64_t staged = 48 * 1024 * std::max<int64_t>(1, v / 2048);
     int block = 256;
     while (block < 1024) {
       const int64_t wgs = (v + (int64_t)block * unroll - 1) / ((int64_t)block * unroll);
-      if (wgs == 1 || wgs * (int64_t)lds <= 48 * 1024) break;
+      if (wgs == 1 || wgs * (int64_t)lds <= staged) break;
       block *= 2;
     }
-    return small_shape(c, unroll, block, lds, n4, num_cu);
+    if (small || block < 1024) return small_shape(c, unroll, block, lds, n4, num_cu);
   }
   const int64_t staged = std::min<int64_t>(kMaxPointsPerWG, 11 * (int64_t)lds / 4);
   return stream_shape(c, lds, std::max(kMinPointsPerWG, staged), n4, n, num_cu);
