@@ -129,11 +129,12 @@ __global__ __launch_bounds__(kScanThreads) void k_invert_knots(BuildParams bp, T
   // (The samples are taken while the totals arrive.)
   const double tot = tid < bp.G ? td.totals[tid] : 0.0;
   sample_block(bp, blk, s_d);
-  const double run = block_max_scan(block_scan(tot, s_w[0]), s_w[1]);
+  const double sum = block_scan(tot, s_w[0]);
+  const double run = block_max_scan(sum, s_w[1]);   // (fmax passes NaN over: S_M keeps the sum's)
   if (tid == 0 && blk == 0) s_off[0] = 0.0;
   if (tid == blk - 1) s_off[0] = run;
   if (tid == blk) s_off[1] = run;
-  if (tid == bp.G - 1) s_off[2] = run;
+  if (tid == bp.G - 1) s_off[2] = (sum == sum) ? run : sum;
   s_S[tid] = block_scan(block_cell(bp, blk, s_d), s_w[2]);
   __syncthreads();
   const double off = s_off[0], next = s_off[1], total = s_off[2];
@@ -146,9 +147,10 @@ __global__ __launch_bounds__(kScanThreads) void k_invert_knots(BuildParams bp, T
     return;
   }
   // the targets i S_M / N in (off, next], and one more to either side for
-  // the rounding of the bounds
-  const double per = (double)bp.N / total;
-  const int i0 = max(1, (int)fmin(off * per, (double)bp.N) - 1), i1 = min(bp.N - 1, (int)fmin(next * per, (double)bp.N) + 1);
+  // the rounding of the bounds (S_M is far from denormal: the least density
+  // is 4.9e-324^(2/5) on cells of an FP32 domain)
+  const int i0 = max(1, (int)(off / total * (double)bp.N) - 1);
+  const int i1 = min(bp.N - 1, (int)(next / total * (double)bp.N) + 1);
   const double dt = (bp.b - bp.a) / (double)bp.M;
   const double snap = 1e-12 * (bp.b - bp.a);
   for (int i = i0 + tid; i <= i1; i += kScanThreads) {

@@ -378,9 +378,12 @@ LaunchShape backward_shape(const EvalTable& t, const float* x, const float* g, c
   const LaunchConfig c = g_launch[PWL_KERNEL_BACKWARD];
   const size_t lds = eval_lds_bytes(t.N, t.K, wdv);
   const int64_t n4 = vec ? n / 4 : 0, v = (n4 + num_cu - 1) / num_cu;   // v: vectors per CU
+  // (one workgroup per CU whatever the tuned shape allows: a small launch
+  // needs no more partial sums than that)
+  const LaunchConfig one{c.unroll, c.block, 1};
   if (is_small(c, n4, num_cu) && v <= 512)
-    return small_shape(c, 1, (v <= 256 && t.N <= 1024) ? 256 : 512, lds, n4, num_cu);
-  if (is_small(c, n4, num_cu) && v <= 1024) return small_shape(c, 2, 512, lds, n4, num_cu);
+    return small_shape(one, 1, (v <= 256 && t.N <= 1024) ? 256 : 512, lds, n4, num_cu);
+  if (is_small(c, n4, num_cu) && v <= 1024) return small_shape(one, 2, 512, lds, n4, num_cu);
   return stream_shape(c, lds, std::max<int64_t>(kMinPointsPerWG, kPointsPerStagedByte * (int64_t)lds), n4, n, num_cu);
 }
 

@@ -195,3 +195,24 @@ def test_projection_across_workgroup_rows(N):
             yr = O.evaluate(X, d["values"].astype(np.float64), x.astype(np.float64))
             assert np.max(np.abs(y - yr)) <= 2e-6 * fmax_abs(func, p, a, b)
             t.free()
+
+
+@pytest.mark.parametrize("N", [5, 300, 4096])
+def test_overflowing_density_falls_back_to_uniform(N):
+    """f'' that overflows (infinities, and NaN where they meet an exp that
+    underflows) leaves no finite density integral: the knots are uniform and
+    the flag says so, wherever in the domain the overflow lies."""
+    import paper_1510_02975_amd as P
+    library()
+    device()
+    for a, b in ((-5.0, 5.0), (-1e-3, 6.0), (-6.0, 0.0)):
+        t = P.pwl_build(O.GAUSSIAN, (1e-3, 1e308), a, b, N, O.OPTIMAL, O.INTERP)
+        assert t.flags() == P.FLAG_NONFINITE
+        a32, b32 = (float(np.float32(v)) for v in (a, b))
+        assert np.array_equal(P.pwl_table_download(t)["knots"], O.uniform_knots(a32, b32, N)[0].astype(np.float32))
+        t.free()
+    # the smallest second derivative there is still finds its knots
+    t = P.pwl_build(O.GAUSSIAN, (1.0, 5e-324), -1.0, 1.0, N, O.OPTIMAL, O.INTERP)
+    k = P.pwl_table_download(t)["knots64"]
+    assert np.all(np.diff(k) > 0) and k[0] == -1.0 and k[-1] == 1.0
+    t.free()
