@@ -25,8 +25,9 @@ namespace {
 constexpr size_t kLdsPerCU = 160 * 1024;
 constexpr int kXcds = 8;             // MI355X accelerator complex dies; workgroups go to them round-robin
 constexpr int64_t kMinPointsPerWG = int64_t(1) << 15;   // streaming grids: points per workgroup, at least
-constexpr int64_t kMaxPointsPerWG = 57344;              // (forward) no more asked for by the staged bytes
-constexpr int64_t kPointsPerStagedByte = 2;             // (backward) and per byte of table the workgroup stages
+constexpr int64_t kMaxPointsPerWG = 57344;              // (forward, N <= 2048) no more asked for by the staged bytes
+constexpr int64_t kPointsPerStagedByte = 2;             // and per byte of table the workgroup stages
+constexpr int kWordsPerThread = 3;                      // tables staged through registers: records per thread
 
 using namespace stream;
 
@@ -35,21 +36,19 @@ constexpr int kVec = 1;      // the arrays are 4-byte aligned: 16-byte accesses
 constexpr int kSearch = 2;   // PWL_LOCATE_SEARCH
 constexpr int kBlockBit = 8;
 
-template <int U, bool ONCE, class S>
+template <int U, bool WORDS, class S>
 __device__ __forceinline__ void eval_fwd_body(const EvalTable& t, const float* __restrict__ vo, const S& s,
                                               const float* __restrict__ x, float* __restrict__ y, int64_t n,
                                               int flags) {
   const int nt = flags >> kBlockBit;
   const int64_t blk = blockIdx.x, nblk = gridDim.x;
   const bool vec = (flags & kVec) != 0;
-  if constexpr (ONCE) {
-    stage_once(t, vo, s);
-    __syncthreads();
-  } else {
+  if constexpr (WORDS)
+    stage_words(t, vo, nt, s);
+  else
     stage_table(t, vo, nt, s);
-    staged();
-    lds_barrier();
-  }
+  staged();
+  lds_barrier();
   if (flags & kSearch) {
     fwd_range<U, -1>(t, s, x, y, 0, n, vec, blk, nblk, nt);
     return;
@@ -65,20 +64,22 @@ __device__ __forceinline__ void eval_fwd_body(const EvalTable& t, const float* _
 }
 
 // REC is the arrangement of the per-segment data in LDS (pwl_set_records):
-// packed records, structure of arrays, or value/slope pairs; ONCE: a
-// structure-of-arrays image whose sections fit in one word per thread.  Its
-// staging is the shorter one to wait for, but what keeps it apart is the
-// register allocation of the streaming loop, which the compiler decides for
-// the whole kernel: with the general staging beside it the loop takes 104
-// registers instead of 90 and runs 341 us instead of 332 at N = 1024, 2^28
-// points.
-template <int U, int REC, bool ONCE>
+// packed records, structure of arrays, or value/slope pairs; WORDS: a
+// structure-of-arrays image of at most kWordsPerThread records per thread,
+// staged through registers.  What keeps the two stagings apart is the
+// streaming loop, whose schedule and registers the compiler decides for the
+// whole kernel: beside the register staging it takes 90 registers and starts
+// half of its lookups before the last loads arrive, beside the copy 104.  In
+// us, registers / copy: Gaussian N = 1024, 2^28 points 332 / 341; 2^27 points
+// Lorentzian N = 1024 178.8 / 183.9, 2000 182.5 / 187.2, 2500 188.9 / 194.5,
+// 4096 195.9 / 195.0; J0 N = 1500 169.9 / 174.8, 4096 183.6 / 181.4.
+template <int U, int REC, bool WORDS>
 __global__ __launch_bounds__(1024) void k_eval_fwd(EvalTable t, const float* __restrict__ vo,
                                                    const float* __restrict__ x,
                                                    float* __restrict__ y, int64_t n, int flags) {
   extern __shared__ float4 lds_f4[];
   if constexpr (REC == PWL_RECORDS_SOA)
-    eval_fwd_body<U, ONCE>(t, vo, carve_soa(lds_f4, t.N), x, y, n, flags);
+    eval_fwd_body<U, WORDS>(t, vo, carve_soa(lds_f4, t.N), x, y, n, flags);
   else if constexpr (REC == PWL_RECORDS_PAIRS)
     eval_fwd_body<U, false>(t, vo, carve_pairs(lds_f4, t.N), x, y, n, flags);
   else
@@ -218,9 +219,12 @@ inline bool word_aligned(const void* p) { return (reinterpret_cast<uintptr_t>(p)
 // vectors in 3 per CU).  pwl_set_launch overrides them.
 //
 // Enough points, forward: 2^15, and 2.75 per byte of the image up to 57344.
-// At 2^28 points N = 16 takes 32 per CU (328 us; 18: 334) and N = 1024 and
-// 4096 take 18 (333 and 346 us; 25 per CU 335 and 352, 3 per CU 360); N = 4096
-// at 2^27 points 9 (177 us; 3: 181, 18: 185).
+// At 2^28 points N = 16 takes 32 per CU (328 us; 18: 334) and N = 1024 18
+// (333 us; 25: 335); at 2^27 the Lorentzian with N = 2000 9 (182.5 us; 6:
+// 184.0, 4: 187.1).  Above N = 2048 the map is not widened where knots crowd,
+// such tables compare three knots per point and a third round of lookups
+// competes with the staging: 2 points per byte (N = 4096, 2^27 points: 3 per
+// CU, Lorentzian 195.0 us and J0 181.4; 9 per CU 208.7 and 177.5).
 //
 // A launch too small to give every CU a workgroup of the tuned shape spreads
 // over the CUs instead, in smaller workgroups with fewer vectors per thread.
@@ -265,7 +269,7 @@ bool is_small(const LaunchConfig& c, int64_t n4, int num_cu) {
   return n4 > 0 && n4 < (int64_t)num_cu * c.block * c.unroll;
 }
 
-LaunchShape forward_shape(size_t lds, int64_t n4, int64_t n, int num_cu) {
+LaunchShape forward_shape(int N, size_t lds, int64_t n4, int64_t n, int num_cu) {
   const LaunchConfig c = g_launch[PWL_KERNEL_FORWARD];
   const int64_t v = (n4 + num_cu - 1) / num_cu;   // vectors per CU
   const bool small = is_small(c, n4, num_cu);
@@ -280,7 +284,8 @@ LaunchShape forward_shape(size_t lds, int64_t n4, int64_t n, int num_cu) {
     }
     if (small || block < 1024) return small_shape(c, unroll, block, lds, n4, num_cu);
   }
-  const int64_t staged = std::min<int64_t>(kMaxPointsPerWG, 11 * (int64_t)lds / 4);
+  const int64_t staged = N <= kWideMapMaxN ? std::min<int64_t>(kMaxPointsPerWG, 11 * (int64_t)lds / 4)
+                                           : kPointsPerStagedByte * (int64_t)lds;
   return stream_shape(c, lds, std::max(kMinPointsPerWG, staged), n4, n, num_cu);
 }
 
@@ -325,7 +330,7 @@ hipError_t launch_eval(const EvalTable& t, const float* vo, const float* x, floa
   const size_t lds = rec == PWL_RECORDS_SOA     ? eval_lds_bytes_soa(t.N, t.K)
                      : rec == PWL_RECORDS_PAIRS ? eval_lds_bytes_pairs(t.N, t.K)
                                                 : eval_lds_bytes(t.N, t.K, false);
-  const LaunchShape ls = forward_shape(lds, vec ? n / 4 : 0, n, num_cu);
+  const LaunchShape ls = forward_shape(t.N, lds, vec ? n / 4 : 0, n, num_cu);
   const int v = (vec ? kVec : 0) | (g_locate == PWL_LOCATE_SEARCH ? kSearch : 0) | (ls.block << kBlockBit);
 #define PWL_FWD(UU, RR, OO) \
   hipLaunchKernelGGL((k_eval_fwd<UU, RR, OO>), dim3(ls.grid), dim3(ls.block), ls.lds, s, t, vo, x, y, n, v)
@@ -336,7 +341,7 @@ hipError_t launch_eval(const EvalTable& t, const float* vo, const float* x, floa
     default: PWL_FWD(4, RR, OO); break;     \
   }
   if (rec == PWL_RECORDS_SOA) {
-    if (std::max({t.N, image_knot_words(t.N), image_map_words(t.K)}) <= ls.block) {
+    if (t.N <= kWordsPerThread * ls.block) {
       PWL_FWD_U(PWL_RECORDS_SOA, true)
     } else {
       PWL_FWD_U(PWL_RECORDS_SOA, false)

@@ -138,9 +138,11 @@ __device__ __forceinline__ void stage_copy(const void* __restrict__ src, int n, 
   }
 }
 
-// The structure-of-arrays image when each of its sections fits in one word
-// per thread: every thread loads its words before it writes any.
-__device__ __forceinline__ void stage_once(const EvalTable& t, const float* __restrict__ vo, const SmemSoA& s) {
+// The structure-of-arrays image through registers where it is not much
+// larger than the workgroup: every thread loads its first word of each
+// section before it writes any, and the rest follows (staged() ends it).
+__device__ __forceinline__ void stage_words(const EvalTable& t, const float* __restrict__ vo, int nt,
+                                            const SmemSoA& s) {
   const int tid = threadIdx.x;
   const int nkw = image_knot_words(t.N), nmw = image_map_words(t.K);
   float4* knot4 = reinterpret_cast<float4*>(s.knot);
@@ -156,6 +158,13 @@ __device__ __forceinline__ void stage_once(const EvalTable& t, const float* __re
   }
   if (hk) knot4[tid] = k;
   if (hm) map4[tid] = m;
+  for (int w = tid + nt; w < t.N; w += nt) {
+    const float4 q = record_word(t, vo, w);
+    s.rv[w] = q.y;
+    s.rs[w] = q.z;
+  }
+  if (nkw > nt) stage_copy(t.knots + 4 * nt, nkw - nt, nt, knot4 + nt);
+  if (nmw > nt) stage_copy(t.lo + 8 * nt, nmw - nt, nt, map4 + nt);
 }
 
 // Waits for the wave's own part of the staging (and its other loads in

@@ -64,7 +64,8 @@ def test_every_phase(n):
     t.free()
 
 
-@pytest.mark.parametrize("N", [63, 64, 127, 255, 256, 511, 512, 1023, 1024, 1025, 2048, 4095, 4096])
+@pytest.mark.parametrize("N", [63, 64, 127, 192, 193, 255, 256, 511, 512, 768, 769, 1023, 1024, 1025, 2048,
+                               3072, 3073, 4095, 4096])
 @pytest.mark.parametrize("shape", [(1, 64, 1), (2, 256, 2), (4, 1024, 32)], ids=["64", "256", "1024"])
 def test_staging_sizes(N, shape):
     """The Lorentzian's map has 8 N cells up to N = 2048 (the map is then the
