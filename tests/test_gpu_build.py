@@ -216,3 +216,24 @@ def test_overflowing_density_falls_back_to_uniform(N):
     k = P.pwl_table_download(t)["knots64"]
     assert np.all(np.diff(k) > 0) and k[0] == -1.0 and k[-1] == 1.0
     t.free()
+
+
+@pytest.mark.parametrize("N", [2, 15, 64, 65, 300, 1024, 4096])
+def test_map_cells_of_long_segments(N):
+    """Segments of many map cells (tails, where knots are sparse) are written
+    by whole waves: every cell's segment is right, at the knots, beside them
+    and inside every cell (8 N is a multiple of each map's size, and 3 points
+    per eighth leave no cell out), against the oracle's search."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    for func, p, a, b in ((O.GAUSSIAN, (0.3, 1.0), -5.0, 5.0), (O.GAUSSIAN, (0.6, 1.0), -5.0, 5.0),
+                          (O.GAUSSIAN, (0.5, 1.0), -9.0, 1.0), (O.LORENTZIAN, (0.2, 1.0), -20.0, 20.0),
+                          (O.EXP, (3.0, 1.0), -6.0, 1.0)):
+        t = P.pwl_build(func, p, a, b, N, O.OPTIMAL, O.INTERP)
+        X = P.pwl_table_download(t)["knots"]
+        x = np.concatenate([X, np.nextafter(X, np.float32(-np.inf)), np.nextafter(X, np.float32(np.inf)),
+                            np.linspace(a, b, 24 * N + 1)]).astype(np.float32)
+        k = P.pwl_locate(t, torch.from_numpy(x).to(dev)).cpu().numpy()
+        assert np.array_equal(k, O.locate(X.astype(np.float64), x.astype(np.float64))), (func, p)
+        t.free()
