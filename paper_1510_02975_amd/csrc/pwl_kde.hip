@@ -15,8 +15,8 @@
 // at f_c - h_c, two products and one FP64 addition.  Neighbouring pixels'
 // differences are near each other and consecutive list entries lie in
 // consecutive banks, so the reads hardly conflict (6% of the LDS cycles).
-// What bounds the kernel is VALU issue - 8.2 instructions per tap, two of
-// them FP64 - so a thread takes kPx pixels of a row: it extracts the bytes
+// What bounds the kernel is VALU issue - 10 instructions per tap in all, two
+// of them FP64 - so a thread takes kPx pixels of a row: it extracts the bytes
 // of a reference pixel once for all of its pixels that have it in their
 // windows, and the next row's loads are in flight while one is summed.
 // 1080 x 1920, T = 16, r = 2: a uniform N = 64 table 1491 us with one table
