@@ -64,15 +64,16 @@ __device__ __forceinline__ void eval_fwd_body(const EvalTable& t, const float* _
 }
 
 // REC is the arrangement of the per-segment data in LDS (pwl_set_records):
-// packed records, structure of arrays, or value/slope pairs; WORDS: a
-// structure-of-arrays image of at most kWordsPerThread records per thread,
-// staged through registers.  What keeps the two stagings apart is the
+// packed records, structure of arrays, or value/slope pairs; WORDS: an image
+// of at most kWordsPerThread records per thread, staged through registers.  What keeps the two stagings apart is the
 // streaming loop, whose schedule and registers the compiler decides for the
-// whole kernel: beside the register staging it takes 90 registers and starts
-// half of its lookups before the last loads arrive, beside the copy 104.  In
+// whole kernel: beside the register staging it takes 84 - 90 registers and starts
+// half of its lookups before the last loads arrive, beside the copy 102 - 104.  In
 // us, registers / copy: Gaussian N = 1024, 2^28 points 332 / 341; 2^27 points
 // Lorentzian N = 1024 178.8 / 183.9, 2000 182.5 / 187.2, 2500 188.9 / 194.5,
-// 4096 195.9 / 195.0; J0 N = 1500 169.9 / 174.8, 4096 183.6 / 181.4.
+// 4096 195.9 / 195.0; J0 N = 1500 169.9 / 174.8, 4096 183.6 / 181.4.  Packed
+// records, Gaussian N = 1024, 2^28 points 335.8 / 340.3, by binary search
+// 1411 / 1458; pairs 347.2 / 349.0 and 1386 / 1449.
 template <int U, int REC, bool WORDS>
 __global__ __launch_bounds__(1024) void k_eval_fwd(EvalTable t, const float* __restrict__ vo,
                                                    const float* __restrict__ x,
@@ -81,9 +82,9 @@ __global__ __launch_bounds__(1024) void k_eval_fwd(EvalTable t, const float* __r
   if constexpr (REC == PWL_RECORDS_SOA)
     eval_fwd_body<U, WORDS>(t, vo, carve_soa(lds_f4, t.N), x, y, n, flags);
   else if constexpr (REC == PWL_RECORDS_PAIRS)
-    eval_fwd_body<U, false>(t, vo, carve_pairs(lds_f4, t.N), x, y, n, flags);
+    eval_fwd_body<U, WORDS>(t, vo, carve_pairs(lds_f4, t.N), x, y, n, flags);
   else
-    eval_fwd_body<U, false>(t, vo, carve(lds_f4, t.N, t.K, false), x, y, n, flags);
+    eval_fwd_body<U, WORDS>(t, vo, carve(lds_f4, t.N, t.K, false), x, y, n, flags);
 }
 
 template <int U, bool WY, bool WDX, bool WDV>
@@ -340,17 +341,20 @@ hipError_t launch_eval(const EvalTable& t, const float* vo, const float* x, floa
     case 2: PWL_FWD(2, RR, OO); break;      \
     default: PWL_FWD(4, RR, OO); break;     \
   }
-  if (rec == PWL_RECORDS_SOA) {
-    if (t.N <= kWordsPerThread * ls.block) {
-      PWL_FWD_U(PWL_RECORDS_SOA, true)
-    } else {
-      PWL_FWD_U(PWL_RECORDS_SOA, false)
-    }
-  } else if (rec == PWL_RECORDS_PAIRS) {
-    PWL_FWD_U(PWL_RECORDS_PAIRS, false)
-  } else {
-    PWL_FWD_U(PWL_RECORDS_PACKED, false)
+#define PWL_FWD_R(RR)                       \
+  if (t.N <= kWordsPerThread * ls.block) {  \
+    PWL_FWD_U(RR, true)                     \
+  } else {                                  \
+    PWL_FWD_U(RR, false)                    \
   }
+  if (rec == PWL_RECORDS_SOA) {
+    PWL_FWD_R(PWL_RECORDS_SOA)
+  } else if (rec == PWL_RECORDS_PAIRS) {
+    PWL_FWD_R(PWL_RECORDS_PAIRS)
+  } else {
+    PWL_FWD_R(PWL_RECORDS_PACKED)
+  }
+#undef PWL_FWD_R
 #undef PWL_FWD_U
 #undef PWL_FWD
   return hipGetLastError();
@@ -449,9 +453,11 @@ hipError_t configure_eval_kernels(int max_lds) {
   PWL_ATTR((k_eval_fwd<2, RR, OO>))          \
   PWL_ATTR((k_eval_fwd<4, RR, OO>))
   PWL_ATTR_R(PWL_RECORDS_PACKED, false)
+  PWL_ATTR_R(PWL_RECORDS_PACKED, true)
   PWL_ATTR_R(PWL_RECORDS_SOA, false)
   PWL_ATTR_R(PWL_RECORDS_SOA, true)
   PWL_ATTR_R(PWL_RECORDS_PAIRS, false)
+  PWL_ATTR_R(PWL_RECORDS_PAIRS, true)
 #undef PWL_ATTR_R
 #define PWL_ATTR_U(U)                            \
   PWL_ATTR((k_eval_bwd<U, false, false, true>))  \

@@ -138,35 +138,6 @@ __device__ __forceinline__ void stage_copy(const void* __restrict__ src, int n, 
   }
 }
 
-// The structure-of-arrays image through registers where it is not much
-// larger than the workgroup: every thread loads its first word of each
-// section before it writes any, and the rest follows (staged() ends it).
-__device__ __forceinline__ void stage_words(const EvalTable& t, const float* __restrict__ vo, int nt,
-                                            const SmemSoA& s) {
-  const int tid = threadIdx.x;
-  const int nkw = image_knot_words(t.N), nmw = image_map_words(t.K);
-  float4* knot4 = reinterpret_cast<float4*>(s.knot);
-  float4* map4 = reinterpret_cast<float4*>(s.lo);
-  const bool hr = tid < t.N, hk = tid < nkw, hm = tid < nmw;
-  float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f), k = r, m = r;
-  if (hr) r = record_word(t, vo, tid);
-  if (hk) k = reinterpret_cast<const float4*>(t.knots)[tid];
-  if (hm) m = reinterpret_cast<const float4*>(t.lo)[tid];
-  if (hr) {
-    s.rv[tid] = r.y;
-    s.rs[tid] = r.z;
-  }
-  if (hk) knot4[tid] = k;
-  if (hm) map4[tid] = m;
-  for (int w = tid + nt; w < t.N; w += nt) {
-    const float4 q = record_word(t, vo, w);
-    s.rv[w] = q.y;
-    s.rs[w] = q.z;
-  }
-  if (nkw > nt) stage_copy(t.knots + 4 * nt, nkw - nt, nt, knot4 + nt);
-  if (nmw > nt) stage_copy(t.lo + 8 * nt, nmw - nt, nt, map4 + nt);
-}
-
 // Waits for the wave's own part of the staging (and its other loads in
 // flight); a barrier then makes the whole image visible.
 __device__ __forceinline__ void staged() { __builtin_amdgcn_s_waitcnt(kWaitVm0); }
@@ -226,6 +197,50 @@ __device__ __forceinline__ void stage_table(const EvalTable& t, const float* __r
   stage_rounds(image_pair_words(t.N), nt, [&](int w) { return pair_word(t, vo, w); },
                [&](int w, float4 p) { pair4[w] = p; });
   staged();
+}
+
+// A forward image's record section by words: how many, a word's load and its
+// place.
+__device__ __forceinline__ int section_words(const EvalTable& t, const Smem&) { return t.N; }
+__device__ __forceinline__ int section_words(const EvalTable& t, const SmemSoA&) { return t.N; }
+__device__ __forceinline__ int section_words(const EvalTable& t, const SmemPairs&) { return image_pair_words(t.N); }
+template <class S>
+__device__ __forceinline__ float4 section_word(const EvalTable& t, const float* __restrict__ vo, int w, const S&) {
+  return record_word(t, vo, w);
+}
+__device__ __forceinline__ float4 section_word(const EvalTable& t, const float* __restrict__ vo, int w,
+                                               const SmemPairs&) {
+  return pair_word(t, vo, w);
+}
+__device__ __forceinline__ void put_word(const Smem& s, int w, float4 r) { s.rec[w] = r; }
+__device__ __forceinline__ void put_word(const SmemSoA& s, int w, float4 r) {
+  s.rv[w] = r.y;
+  s.rs[w] = r.z;
+}
+__device__ __forceinline__ void put_word(const SmemPairs& s, int w, float4 p) {
+  reinterpret_cast<float4*>(s.vs)[w] = p;
+}
+
+// An image through registers where it is not much larger than the workgroup:
+// every thread loads its first word of each section before it writes any, and
+// the rest follows (staged() ends it).
+template <class S>
+__device__ __forceinline__ void stage_words(const EvalTable& t, const float* __restrict__ vo, int nt, const S& s) {
+  const int tid = threadIdx.x;
+  const int nrw = section_words(t, s), nkw = image_knot_words(t.N), nmw = image_map_words(t.K);
+  float4* knot4 = reinterpret_cast<float4*>(s.knot);
+  float4* map4 = reinterpret_cast<float4*>(s.lo);
+  const bool hr = tid < nrw, hk = tid < nkw, hm = tid < nmw;
+  float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f), k = r, m = r;
+  if (hr) r = section_word(t, vo, tid, s);
+  if (hk) k = reinterpret_cast<const float4*>(t.knots)[tid];
+  if (hm) m = reinterpret_cast<const float4*>(t.lo)[tid];
+  if (hr) put_word(s, tid, r);
+  if (hk) knot4[tid] = k;
+  if (hm) map4[tid] = m;
+  for (int w = tid + nt; w < nrw; w += nt) put_word(s, w, section_word(t, vo, w, s));
+  if (nkw > nt) stage_copy(t.knots + 4 * nt, nkw - nt, nt, knot4 + nt);
+  if (nmw > nt) stage_copy(t.lo + 8 * nt, nmw - nt, nt, map4 + nt);
 }
 
 __device__ __forceinline__ float clamp_nan(float x, float a, float b) {

@@ -10,7 +10,7 @@ import torch
 
 import oracle as O
 import workloads as W
-from tests.gpu_util import GRAD_TOL, Y_TOL, device, launch_shape, library, say
+from tests.gpu_util import GRAD_TOL, Y_TOL, device, launch_shape, library, records_layout, say
 
 pytestmark = pytest.mark.gpu
 
@@ -123,4 +123,29 @@ def test_small_launch_edges(N, vectors_per_cu):
         assert np.max(np.abs(y.cpu().numpy() - yr)) <= Y_TOL
         assert torch.equal(yb, y)
         assert np.all(np.abs(dv.cpu().numpy() - dvr) <= GRAD_TOL * wk + 1e-30)
+    t.free()
+
+
+@pytest.mark.parametrize("layout", ["packed", "pairs"])
+@pytest.mark.parametrize("N", [1, 2, 63, 64, 65, 191, 192, 193, 767, 768, 769, 1024, 1025, 3071, 3072, 3073, 4096])
+def test_staging_sizes_of_other_records(N, layout):
+    """The other record layouts around the sizes where their image is staged
+    through registers or copied, with the table's values and with given ones."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    t = P.pwl_build(O.LORENTZIAN, (1.0, 1.0), -20.0, 20.0, N, O.OPTIMAL, O.INTERP)
+    d = P.pwl_table_download(t)
+    X = d["knots"].astype(np.float64)
+    xh = np.concatenate([d["knots"], W.uniform_points(-21.0, 21.0, 30011, N)]).astype(np.float32)
+    x = torch.from_numpy(xh).to(dev)
+    vh = (1.0 + 0.5 * np.cos(np.arange(N + 1))).astype(np.float32)
+    vo = torch.from_numpy(vh).to(dev)
+    with records_layout(P, {"packed": P.RECORDS_PACKED, "pairs": P.RECORDS_PAIRS}[layout]):
+        for shape in ((1, 64, 1), (2, 256, 2), (4, 1024, 32)):
+            with launch_shape(P, P.KERNEL_FORWARD, shape):
+                y, yo = P.pwl_eval(t, x), P.pwl_eval(t, x, v_override=vo)
+            for got, v in ((y, d["values"]), (yo, vh)):
+                ref = O.evaluate(X, v.astype(np.float64), xh.astype(np.float64))
+                assert np.max(np.abs(got.cpu().numpy() - ref)) <= Y_TOL * max(1.0, np.max(np.abs(v)))
     t.free()
