@@ -213,7 +213,7 @@ pwl_status pwl_table_info(const pwl_table* t, int32_t* N, double* a, double* b, 
 pwl_status pwl_table_download(const pwl_table* t, float* knots, float* values, double* knots64,
                               double* values64, void* stream);
 
-/* pwl_table_free - release a table (waits for the device to finish with it). NULL is a no-op. */
+/* pwl_table_free - release a table (waits for its device to finish with it; any device may be current). NULL is a no-op. */
 void pwl_table_free(pwl_table* t);
 
 /* ---- evaluation (Algorithm 1, Sec. IV) --------------------------------- */

@@ -553,6 +553,11 @@ pwl_status pwl_table_download(const pwl_table* t, float* knots, float* values, d
 
 void pwl_table_free(pwl_table* t) {
   if (t == nullptr) return;
+  // the waits and the releases are the table's device's, which need not be
+  // the current one (a collector may free tables anywhere)
+  int current = t->device;
+  (void)hipGetDevice(&current);
+  if (current != t->device) (void)hipSetDevice(t->device);
   if (t->part != nullptr) {
     // stream-ordered memory: released once the device is done with it
     (void)hipDeviceSynchronize();
@@ -562,6 +567,7 @@ void pwl_table_free(pwl_table* t) {
   }
   if (t->built) (void)hipEventDestroy(t->built);
   (void)hipFree(t->base);
+  if (current != t->device) (void)hipSetDevice(current);
   delete t;
 }
 
