@@ -238,9 +238,10 @@ pwl_status pwl_eval(const pwl_table* t, const float* v_override, const float* x,
  * y, dx, dv must be non-NULL.  This is the exact derivative of Algorithm 1
  * (the paper gives none): dy/dx is the segment slope, dy/dv_k the hat weight.
  * Workspace: (workgroups x (N+1)) floats owned by the table, taken from
- * the stream-ordered allocator (hipMallocAsync on `stream`) by the first
- * call with dv that needs more (at least doubling); they are freed with the
- * table, outgrown ones too.
+ * the stream-ordered allocator (hipMallocAsync on `stream`; with hipMalloc
+ * while `stream` is being captured, so that they outlive the graph) by the
+ * first call with dv that needs more (doubling where that can be had); they
+ * are freed with the table, outgrown ones too.
  * Calls with dv on one table share them, so they must not overlap in time:
  * issue them on one stream.
  */

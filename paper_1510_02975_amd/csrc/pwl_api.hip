@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -30,6 +31,14 @@ struct pwl_batch {
   hipGraphExec_t exec;
 };
 
+// One allocation of partial sums.
+struct Rows {
+  float* p;
+  size_t cap;    // floats
+  bool pooled;   // from the stream-ordered allocator
+  Rows* older;
+};
+
 struct pwl_table {
   int device;
   int kcap;   // map cells the arena can hold
@@ -38,16 +47,12 @@ struct pwl_table {
   void* base;
   size_t bytes;
   hipEvent_t built = nullptr;   // recorded after every build of the table
-  // dL/dv partial sums of the fused backward (one row per workgroup), taken
-  // from the stream-ordered allocator by the first backward call that needs
-  // more.  Outgrown rows, which calls on other streams may still read, are
-  // kept with the table: a capacity at least doubles, so together they stay
-  // below the current one, and no call has to record an event for them.
-  mutable std::mutex part_mu;
-  mutable float* part = nullptr;
-  mutable size_t part_cap = 0;   // floats
-  mutable float* outgrown[64] = {};
-  mutable int noutgrown = 0;
+  // dL/dv partial sums of the fused backward (one row per workgroup), newest
+  // first: the first call that needs more takes more, and the outgrown ones,
+  // which calls on other streams and captured graphs may still use, are kept
+  // with the table (no call has to record an event for them).
+  mutable std::mutex rows_mu;
+  mutable Rows* rows = nullptr;
 };
 
 namespace {
@@ -327,6 +332,68 @@ pwl_status check_table(const pwl_table* t, int* num_cu) {
   return PWL_OK;
 }
 
+// Whether work on s is being recorded into a graph.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (s != nullptr && hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+  return st == hipStreamCaptureStatusActive;
+}
+
+// Memory for r: in stream order on s, without waiting for the device; while s
+// records a graph, plain device memory, since what the stream-ordered
+// allocator hands out then is the graph's own - there only while the graph
+// runs, where the table keeps its rows for every later call.
+hipError_t take_rows(Rows* r, size_t floats, hipStream_t s) {
+  void* p = nullptr;
+  hipError_t e;
+  r->pooled = !capturing(s);
+  if (r->pooled) {
+    e = hipMallocAsync(&p, floats * sizeof(float), s);
+  } else {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // allocating is allowed on this thread
+    e = hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) {
+      e = hipMalloc(&p, floats * sizeof(float));
+      (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+  }
+  if (e != hipSuccess) (void)hipGetLastError();
+  r->p = static_cast<float*>(p);
+  r->cap = floats;
+  return e;
+}
+
+// Rows of at least `need` floats become the table's current ones (twice what
+// it had, if that can be had).
+pwl_status grow_rows(const pwl_table* t, size_t need, hipStream_t s) {
+  const size_t twice = t->rows != nullptr ? std::max(need, 2 * t->rows->cap) : need;
+  Rows* r = new (std::nothrow) Rows{};
+  if (r == nullptr) return fail(PWL_ENOMEM, "no host memory for the dL/dv partial sums");
+  hipError_t e = take_rows(r, twice, s);
+  if (e != hipSuccess && twice > need) e = take_rows(r, need, s);
+  if (e != hipSuccess) {
+    delete r;
+    return fail(PWL_ENOMEM, "allocating %zu bytes for the dL/dv partial sums failed: %s", need * sizeof(float),
+                hipGetErrorString(e));
+  }
+  r->older = t->rows;
+  t->rows = r;
+  return PWL_OK;
+}
+
+// Gives the table's rows back; its device is current and done with them.
+void free_rows(const pwl_table* t) {
+  while (Rows* r = t->rows) {
+    if (r->pooled)
+      (void)hipFreeAsync(r->p, g_aux[t->device]);
+    else
+      (void)hipFree(r->p);
+    t->rows = r->older;
+    delete r;
+  }
+  (void)hipStreamSynchronize(g_aux[t->device]);
+}
+
 }  // namespace
 
 extern "C" {
@@ -558,12 +625,10 @@ void pwl_table_free(pwl_table* t) {
   int current = t->device;
   (void)hipGetDevice(&current);
   if (current != t->device) (void)hipSetDevice(t->device);
-  if (t->part != nullptr) {
+  if (t->rows != nullptr) {
     // stream-ordered memory: released once the device is done with it
     (void)hipDeviceSynchronize();
-    (void)hipFreeAsync(t->part, g_aux[t->device]);
-    for (int i = 0; i < t->noutgrown; ++i) (void)hipFreeAsync(t->outgrown[i], g_aux[t->device]);
-    (void)hipStreamSynchronize(g_aux[t->device]);
+    free_rows(t);
   }
   if (t->built) (void)hipEventDestroy(t->built);
   (void)hipFree(t->base);
@@ -601,29 +666,13 @@ pwl_status pwl_eval_backward(const pwl_table* t, const float* v_override, const 
     PWL_HIP(pwl::launch_eval_backward(e, v_override, x, g, y, dx, dv, nullptr, n, num_cu, s));
     return PWL_OK;
   }
-  // The partial-sum rows: grown in stream order on the caller's stream,
-  // never by a device-wide synchronisation.
-  std::lock_guard<std::mutex> lock(t->part_mu);
+  std::lock_guard<std::mutex> lock(t->rows_mu);
   const size_t need = pwl::backward_workspace_floats(e, x, g, y, dx, n, num_cu);
-  if (need > t->part_cap) {
-    if (t->noutgrown == (int)(sizeof(t->outgrown) / sizeof(t->outgrown[0])))
-      return fail(PWL_ENOMEM, "the dL/dv partial sums were outgrown too often");
-    size_t cap = std::max(need, 2 * t->part_cap);
-    void* p = nullptr;
-    hipError_t me = hipMallocAsync(&p, cap * sizeof(float), s);
-    if (me != hipSuccess && cap > need) {
-      (void)hipGetLastError();
-      cap = need;
-      me = hipMallocAsync(&p, cap * sizeof(float), s);
-    }
-    if (me != hipSuccess)
-      return fail(PWL_ENOMEM, "hipMallocAsync(%zu) for the dL/dv partial sums failed: %s", cap * sizeof(float),
-                  hipGetErrorString(me));
-    if (t->part != nullptr) t->outgrown[t->noutgrown++] = t->part;
-    t->part = static_cast<float*>(p);
-    t->part_cap = cap;
+  if (t->rows == nullptr || need > t->rows->cap) {
+    st = grow_rows(t, need, s);
+    if (st != PWL_OK) return st;
   }
-  PWL_HIP(pwl::launch_eval_backward(e, v_override, x, g, y, dx, dv, t->part, n, num_cu, s));
+  PWL_HIP(pwl::launch_eval_backward(e, v_override, x, g, y, dx, dv, t->rows->p, n, num_cu, s));
   return PWL_OK;
 }
 

@@ -161,3 +161,46 @@ def test_dv_is_deterministic_and_workspace_grows():
         assert np.all(np.abs(dv.cpu().numpy() - dvr) <= GRAD_TOL * wk + 1e-30)
     assert torch.equal(dv4, dv1)
     t.free()
+
+
+@pytest.mark.parametrize("before", [0, 1000], ids=["first", "outgrown"])
+def test_workspace_taken_under_capture(before):
+    """A captured backward that is the first with dv, or needs more rows than
+    the table has: eager calls (one before any replay) and replays on changed
+    inputs, in turn, all give what another table's eager calls give."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    n = 1 << 20
+    t, ref = (P.pwl_build(O.GAUSSIAN, (1.0, 1.0), -5.0, 5.0, 64, O.OPTIMAL, O.PROJ) for _ in range(2))
+    x_h, g_h = W.grad_inputs(n)
+    x, g = torch.from_numpy(x_h).to(dev), torch.from_numpy(g_h).to(dev)
+    y, dx, dv = torch.empty_like(x), torch.empty_like(x), torch.empty(65, device=dev)
+    if before:
+        P.pwl_eval_backward(t, x[:before], g[:before])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        P.pwl_eval_backward(t, x, g, y=y, dx=dx, dv=dv)
+    eager = P.pwl_eval_backward(t, x, g)
+    want = P.pwl_eval_backward(ref, x, g)
+    for a, b in zip(eager, want):
+        assert torch.equal(a, b)
+    for k in range(3):
+        x.mul_(0.75)
+        g.add_(float(k))
+        for out in (y, dx, dv):
+            out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        want = P.pwl_eval_backward(ref, x, g)
+        for a, b in zip((y, dx, dv), want):
+            assert torch.equal(a, b), k
+        for a, b in zip(P.pwl_eval_backward(t, x, g), want):
+            assert torch.equal(a, b), k
+    torch.cuda.synchronize()
+    del graph
+    for a, b in zip(P.pwl_eval_backward(t, x, g), want):   # the rows outlive the graph
+        assert torch.equal(a, b)
+    t.free()
+    ref.free()

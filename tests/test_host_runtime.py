@@ -24,3 +24,32 @@ result([log(), d.value, H.fake_live()])
     assert ["devicesync", "1"] not in calls
     assert all(calls[i][2] == "0" for i in given_back)            # with the table's device current
     assert current == 1
+
+
+def test_rows_taken_under_capture_are_not_the_graphs(tmp_path):
+    """A workspace that is first needed, or outgrown, while the caller's stream
+    records a graph is device memory of the table's own: what the
+    stream-ordered allocator gives then exists only while the graph runs."""
+    r = fake_hip.run(tmp_path, """
+out = []
+for first in (None, 1000):                  # first needed under capture; outgrown under capture
+    t = build(64)
+    if first:
+        assert backward(t, first) == 0
+    H.fake_capture(0x5000, 1)
+    log()
+    assert backward(t, 1 << 20, 0x5000) == 0, L.pwl_last_error()
+    H.fake_capture(0x5000, 0)
+    out.append(log())
+    log()
+    assert backward(t, 1 << 20) == 0        # later calls use the same rows
+    out.append(log())
+    L.pwl_table_free(t)
+    assert H.fake_live() == 0
+result(out)
+""")
+    for captured, later in (r[:2], r[2:]):
+        kinds = [c[0] for c in captured]
+        assert "graphmalloc" not in kinds and kinds.count("malloc") == 1, kinds
+        assert kinds.count("launch") == 2
+        assert [c[0] for c in later] == ["launch", "launch"]
