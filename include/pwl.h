@@ -240,8 +240,10 @@ pwl_status pwl_eval(const pwl_table* t, const float* v_override, const float* x,
  * Workspace: (workgroups x (N+1)) floats owned by the table, taken from
  * the stream-ordered allocator (hipMallocAsync on `stream`; with hipMalloc
  * while `stream` is being captured, so that they outlive the graph) by the
- * first call with dv that needs more (doubling where that can be had); they
- * are freed with the table, outgrown ones too.
+ * first call with dv that needs more (doubling); they are freed with the
+ * table, outgrown ones too.  Where memory is too short for that, the call
+ * waits for the device, frees those that no captured graph uses and takes
+ * what it needs.
  * Calls with dv on one table share them, so they must not overlap in time:
  * issue them on one stream.
  */

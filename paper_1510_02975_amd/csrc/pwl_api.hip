@@ -36,6 +36,7 @@ struct Rows {
   float* p;
   size_t cap;    // floats
   bool pooled;   // from the stream-ordered allocator
+  bool graphs;   // used by a captured graph
   Rows* older;
 };
 
@@ -48,9 +49,11 @@ struct pwl_table {
   size_t bytes;
   hipEvent_t built = nullptr;   // recorded after every build of the table
   // dL/dv partial sums of the fused backward (one row per workgroup), newest
-  // first: the first call that needs more takes more, and the outgrown ones,
-  // which calls on other streams and captured graphs may still use, are kept
-  // with the table (no call has to record an event for them).
+  // first: the first call that needs more takes twice as much, and the outgrown
+  // ones, which calls on other streams and captured graphs may still use, are
+  // kept with the table (no call has to record an event for them): together
+  // they stay below the current one.  Where memory is too short for that, the
+  // device is waited for and those no graph uses are given back.
   mutable std::mutex rows_mu;
   mutable Rows* rows = nullptr;
 };
@@ -363,14 +366,39 @@ hipError_t take_rows(Rows* r, size_t floats, hipStream_t s) {
   return e;
 }
 
-// Rows of at least `need` floats become the table's current ones (twice what
-// it had, if that can be had).
+// Gives back the table's rows (those of graphs too if `all`); its device is
+// current and done with them.
+void free_rows(const pwl_table* t, bool all) {
+  for (Rows** at = &t->rows; Rows* r = *at;) {
+    if (r->graphs && !all) {
+      at = &r->older;
+      continue;
+    }
+    if (r->pooled)
+      (void)hipFreeAsync(r->p, g_aux[t->device]);
+    else
+      (void)hipFree(r->p);
+    *at = r->older;
+    delete r;
+  }
+  (void)hipStreamSynchronize(g_aux[t->device]);
+}
+
+// Rows of at least `need` floats become the table's current ones.
 pwl_status grow_rows(const pwl_table* t, size_t need, hipStream_t s) {
   const size_t twice = t->rows != nullptr ? std::max(need, 2 * t->rows->cap) : need;
   Rows* r = new (std::nothrow) Rows{};
   if (r == nullptr) return fail(PWL_ENOMEM, "no host memory for the dL/dv partial sums");
   hipError_t e = take_rows(r, twice, s);
-  if (e != hipSuccess && twice > need) e = take_rows(r, need, s);
+  if (e != hipSuccess && t->rows != nullptr) {
+    if (r->pooled) {
+      if (hipDeviceSynchronize() == hipSuccess)
+        free_rows(t, false);
+      else
+        (void)hipGetLastError();
+    }
+    e = take_rows(r, need, s);
+  }
   if (e != hipSuccess) {
     delete r;
     return fail(PWL_ENOMEM, "allocating %zu bytes for the dL/dv partial sums failed: %s", need * sizeof(float),
@@ -379,19 +407,6 @@ pwl_status grow_rows(const pwl_table* t, size_t need, hipStream_t s) {
   r->older = t->rows;
   t->rows = r;
   return PWL_OK;
-}
-
-// Gives the table's rows back; its device is current and done with them.
-void free_rows(const pwl_table* t) {
-  while (Rows* r = t->rows) {
-    if (r->pooled)
-      (void)hipFreeAsync(r->p, g_aux[t->device]);
-    else
-      (void)hipFree(r->p);
-    t->rows = r->older;
-    delete r;
-  }
-  (void)hipStreamSynchronize(g_aux[t->device]);
 }
 
 }  // namespace
@@ -628,7 +643,7 @@ void pwl_table_free(pwl_table* t) {
   if (t->rows != nullptr) {
     // stream-ordered memory: released once the device is done with it
     (void)hipDeviceSynchronize();
-    free_rows(t);
+    free_rows(t, true);
   }
   if (t->built) (void)hipEventDestroy(t->built);
   (void)hipFree(t->base);
@@ -672,6 +687,7 @@ pwl_status pwl_eval_backward(const pwl_table* t, const float* v_override, const 
     st = grow_rows(t, need, s);
     if (st != PWL_OK) return st;
   }
+  if (capturing(s)) t->rows->graphs = true;
   PWL_HIP(pwl::launch_eval_backward(e, v_override, x, g, y, dx, dv, t->rows->p, n, num_cu, s));
   return PWL_OK;
 }

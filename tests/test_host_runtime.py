@@ -53,3 +53,37 @@ result(out)
         assert "graphmalloc" not in kinds and kinds.count("malloc") == 1, kinds
         assert kinds.count("launch") == 2
         assert [c[0] for c in later] == ["launch", "launch"]
+
+
+def test_rows_grow_in_short_memory(tmp_path):
+    """With no memory for twice the rows a call takes what it needs, however
+    often, after giving the outgrown ones back (all but those a captured graph
+    uses), as when each growth freed the rows before it."""
+    r = fake_hip.run(tmp_path, """
+t = build(64)
+base = H.fake_live()
+need = lambda k: 4 * 65 * k                    # k workgroups of 256 threads: 1024 k points
+live, waited = [], []
+for k in range(1, 101):
+    H.fake_malloc_limit(need(k))
+    log()
+    H.fake_capture(0x5000, int(k == 7))
+    st = backward(t, 1024 * k, 0x5000)
+    H.fake_capture(0x5000, 0)
+    assert st == 0, (k, st, L.pwl_last_error())
+    calls = log()
+    given = [i for i, c in enumerate(calls) if c[0].startswith("free")]
+    waited.append(not given or "devicesync" in [c[0] for c in calls[:given[0]]])
+    live.append(H.fake_live() - base)
+H.fake_malloc_limit(need(100) - 4)
+refused = backward(t, 1024 * 120)
+H.fake_malloc_limit(1 << 40)
+after = backward(t, 1024 * 100)
+L.pwl_table_free(t)
+result([live, waited, refused, after, H.fake_live()])
+""")
+    live, waited, refused, after, end = r
+    assert live[:6] == [1, 2, 1, 1, 1, 1]      # (the second is twice the first); growth gave the outgrown back ...
+    assert max(live[6:8]) == 2 and live[8:] == [2] * 92   # ... but not under capture, nor the graph's
+    assert all(waited)
+    assert refused == -2 and after == 0 and end == 0
