@@ -35,9 +35,7 @@ using namespace stream;
 
 constexpr int kKdeThreads = 256;
 constexpr int kPx = 4;                      // consecutive pixels of a row per thread
-constexpr int kTileLanes = 16;              // lanes along a row; the wave's other 4 along y
-constexpr int kTileW = kTileLanes * kPx;    // a wave's tile: 64 x 4 pixels
-constexpr int kTileH = 64 / kTileLanes;
+constexpr int kTileBits = 4;                // a wave's tile: at most 2^4 lanes along a row (64 x 4 pixels)
 constexpr int kWaves = kKdeThreads / 64;
 constexpr int kListLen = 512;               // differences -255 .. 255 of one channel
 
@@ -80,12 +78,13 @@ __device__ __forceinline__ float tap(const char* list, const int (&at)[3], int h
   return g0 * g1 * g2;
 }
 
-// R >= 0: the window radius; -1: any radius, from r.  S waves of a workgroup
-// share a tile, each with its part of the reference frames.
+// R >= 0: the window radius; -1: any radius, from r.  A wave's tile has 2^bits
+// lanes along a row and the others along y.  S waves of a workgroup share a
+// tile, each with its part of the T (2r+1) rows of the windows.
 template <int R, int S>
 __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, const uint32_t* __restrict__ frame,
                                                      const uint32_t* __restrict__ hist, int H, int W, int T,
-                                                     int r, float is0, float is1, float is2,
+                                                     int r, int bits, float is0, float is1, float is2,
                                                      float* __restrict__ out) {
   __shared__ float s_list[3 * kListLen];
   __shared__ double s_part[S > 1 ? kWaves * 64 * kPx : 1];
@@ -96,8 +95,8 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
   }
   __syncthreads();
   const int wave = tid >> 6, lane = tid & 63, part = wave % S;
-  const int x0 = blockIdx.x * kTileW + (lane % kTileLanes) * kPx;
-  const int y = blockIdx.y * (kTileH * kWaves / S) + (wave / S) * kTileH + lane / kTileLanes;
+  const int x0 = ((blockIdx.x << bits) + (lane & ((1 << bits) - 1))) * kPx;
+  const int y = ((blockIdx.y * (kWaves / S) + wave / S) << (6 - bits)) + (lane >> bits);
   double sum[kPx] = {};
   if (x0 < W && y < H) {
     const char* list = reinterpret_cast<const char*>(s_list);
@@ -109,18 +108,23 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
       at[j][1] = 4 * (255 + kListLen + (int)((p >> 8) & 255u));
       at[j][2] = 4 * (255 + 2 * kListLen + (int)((p >> 16) & 255u));
     }
-    const int k1 = (int)((int64_t)T * (part + 1) / S);
-    for (int k = (int)((int64_t)T * part / S); k < k1; ++k) {
+    // window rows [i0, i1): frame i / (2r+1), row i % (2r+1) - r of the window
+    const int w = 2 * r + 1;
+    const int64_t n = (int64_t)T * w, i0 = n * part / S, i1 = n * (part + 1) / S;
+    const int k0 = S > 1 ? (int)(i0 / w) : 0, k1 = S > 1 ? (int)((i1 + w - 1) / w) : T;
+    for (int k = k0; k < k1; ++k) {
       const uint32_t* __restrict__ hk = hist + (int64_t)k * H * W;
+      const int dy0 = S > 1 && k == k0 ? (int)(i0 - (int64_t)k * w) - r : -r;
+      const int dy1 = S > 1 && k == k1 - 1 ? (int)(i1 - (int64_t)k * w) - r - 1 : r;   // the last row
       if constexpr (R >= 0) {
         // one row of the window at a time, the next row's loads in flight
         const bool inside = x0 >= R && x0 + kPx + R <= W;
         auto row = [&](int dy) { return hk + (int64_t)min(max(y + dy, 0), H - 1) * W; };
         uint32_t h[kPx + 2 * R], hn[kPx + 2 * R];
-        load_row<R>(row(-R), x0, W, inside, h);
+        load_row<R>(row(dy0), x0, W, inside, h);
 #pragma unroll 1
-        for (int dy = -R; dy <= R; ++dy) {
-          load_row<R>(row(min(dy + 1, R)), x0, W, inside, hn);
+        for (int dy = dy0; dy <= dy1; ++dy) {
+          load_row<R>(row(min(dy + 1, dy1)), x0, W, inside, hn);
 #pragma unroll
           for (int c = 0; c < kPx + 2 * R; ++c) {
             const int h0 = 4 * (int)(h[c] & 255u), h1 = 4 * (int)((h[c] >> 8) & 255u),
@@ -133,7 +137,7 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
           for (int c = 0; c < kPx + 2 * R; ++c) h[c] = hn[c];
         }
       } else {
-        for (int dy = -r; dy <= r; ++dy) {
+        for (int dy = dy0; dy <= dy1; ++dy) {
           const uint32_t* __restrict__ row = hk + (int64_t)min(max(y + dy, 0), H - 1) * W;
           for (int c = 0; c < kPx + 2 * r; ++c) {
             const uint32_t h = row[min(max(x0 - r + c, 0), W - 1)];
@@ -146,7 +150,7 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
       }
     }
   }
-  if constexpr (S > 1) {   // the parts' sums, added in frame order
+  if constexpr (S > 1) {   // the parts' sums, added in order
 #pragma unroll
     for (int j = 0; j < kPx; ++j) s_part[(wave * kPx + j) * 64 + lane] = sum[j];
     __syncthreads();
@@ -165,22 +169,40 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
 template <int R>
 void launch_kde_r(const EvalTable& t, int mode, const uint32_t* f, const uint32_t* h, int H, int W, int T, int r,
                   float is0, float is1, float is2, float* out, int num_cu, hipStream_t s) {
-  const unsigned gx = (unsigned)((W + kTileW - 1) / kTileW);
-  const int64_t tiles = (int64_t)gx * ((H + kTileH - 1) / kTileH);
+  // The widest tile that pads the rows by at most an eighth, since what a tile
+  // has beyond the image is computed all the same; one lane along a row (whose
+  // lanes each read a row of their own) only where two would pad a seventh more.
+  // 10^6 pixels of uniformly distributed bytes, 64-pixel tiles -> these, T = 16,
+  // r = 2: W = 1 4050 -> 850 us, 16 436 -> 222, 33 306 -> 250, 65 427 -> 233, 97
+  // 288 -> 231; T = 2, r = 1: W = 16 27 -> 14, 65 25 -> 18.  Wide images the same
+  // either way.
+  int bits = kTileBits;
+  auto columns = [&](int b) { return ((int64_t)W + (kPx << b) - 1) / (kPx << b); };
+  auto padded = [&](int b) { return columns(b) * (kPx << b); };
+  while (bits > 0 && padded(bits) > (int64_t)W + W / 8) --bits;
+  if (bits == 0 && 7 * padded(1) <= 8 * padded(0)) bits = 1;
+  const int th = 64 >> bits;
+  const unsigned gx = (unsigned)columns(bits);
+  const int64_t tiles = (int64_t)gx * ((H + th - 1) / th);
   auto launch = [&](auto kernel, int S) {
-    const int rows = kTileH * kWaves / S;
+    const int rows = th * kWaves / S;
     hipLaunchKernelGGL(kernel, dim3(gx, (unsigned)((H + rows - 1) / rows)), dim3(kKdeThreads), 0, s, t, mode, f, h, H,
-                       W, T, r, is0, is1, is2, out);
+                       W, T, r, bits, is0, is1, is2, out);
   };
   // One wave per tile leaves a small image with few waves, and a mid-sized
-  // one with an uneven last round (24 waves fit a CU): the frames are then
-  // split over 2 or 4 waves.  With at least 100 taps per part (16 frames,
-  // r = 2) it pays up to 60 waves per CU - 288 x 352 62 -> 26 us, 480 x 640
-  // 87 -> 56, 900 x 1440 233 -> 205, 720 x 1280 151 -> 147; 1080 x 1920, past
-  // it, 295 -> 300 - and with fewer up to 16: 240 x 320 in 4 frames 18.9 ->
-  // 11.6 us, but 720 x 1280 in 4 frames at r = 1 22.9 -> 26.9.
+  // one with an uneven last round (24 waves fit a CU): the rows of all windows
+  // are then split over 2 or 4 waves.  With at least 100 taps per part (16
+  // frames, r = 2; one frame, r = 10) it pays up to 60 waves per CU, with fewer
+  // up to 16.  One wave per tile -> the split chosen, uniformly distributed
+  // bytes: 288 x 352 T = 16, r = 2 67 -> 32 us, T = 1, r = 32 1363 -> 378;
+  // 480 x 640 T = 16, r = 2 115 -> 74, T = 1, r = 4 34 -> 23; 720 x 1280 T = 16,
+  // r = 2 227 -> 207; past it 1080 x 1920 439 (437 in 4 parts); fewer taps: 480 x
+  // 640 T = 2, r = 2 17.6 -> 14.6, past it 720 x 1280 T = 1, r = 1 9.5 (12.4 in
+  // 4 parts).
   const int64_t taps = (int64_t)T * (2 * r + 1) * (2 * r + 1);
-  auto splits = [&](int S) { return T >= S && tiles * S <= (int64_t)num_cu * (taps >= 100 * S ? 60 : 16); };
+  auto splits = [&](int S) {
+    return (int64_t)T * (2 * r + 1) >= S && tiles * S <= (int64_t)num_cu * (taps >= 100 * S ? 60 : 16);
+  };
   if (splits(4))
     launch(k_kde<R, 4>, 4);
   else if (splits(2))

@@ -100,3 +100,34 @@ def test_kde_tile_edges(H, W_, T, r):
         got = P.pwl_kde(t, mode, f, h, r, sigma).cpu().numpy()
         assert np.max(np.abs(got - ref)) <= 1e-6
     t.free()
+
+
+def _against_oracle(P, dev, H, W_, T, r):
+    f_h, h_h = W.kde_frames(max(H, 12), max(W_, 12), T, seed=6)
+    f_h, h_h = np.ascontiguousarray(f_h[:H, :W_]), np.ascontiguousarray(h_h[:, :H, :W_])
+    f_h[0, 0], h_h[:, H // 2, 0] = (0, 255, 0, 255), (255, 0, 255, 255)
+    say("  kde %dx%d T=%d r=%d" % (H, W_, T, r))
+    sigma = (6.0, 9.5, 31.0)
+    got = P.pwl_kde(None, P.KDE_EXPF, torch.from_numpy(f_h).to(dev), torch.from_numpy(h_h).to(dev), r, sigma)
+    assert np.max(np.abs(got.cpu().numpy() - O.kde_likelihood(f_h, h_h, r, sigma))) <= 1e-6
+
+
+@pytest.mark.parametrize("T,r", [(1, 0), (1, 1), (1, 3), (1, 4), (1, 20), (2, 3), (3, 2), (5, 2)])
+@pytest.mark.parametrize("W_", [1, 2, 4, 5, 8, 9, 16, 17, 32, 33, 61, 64, 65, 100, 131])
+def test_kde_widths(W_, T, r):
+    """Every width of a wave's tile, with its edges, and window rows split
+    over the waves of a workgroup at any row, one frame's rows too."""
+    import paper_1510_02975_amd as P
+    library()
+    _against_oracle(P, device(), 37, W_, T, r)
+
+
+@pytest.mark.parametrize("waves_per_cu,T,r", [(6, 2, 3), (9, 2, 3), (6, 3, 1), (9, 3, 1), (6, 1, 3), (9, 1, 3), (9, 2, 4)])
+def test_kde_splits_of_large_images(waves_per_cu, T, r):
+    """Images of enough tiles (64 rows of one pixel each) for two waves per
+    tile (up to 8 tiles per compute unit at these few taps) or one."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    _against_oracle(P, dev, 64 * cus * waves_per_cu - 7, 1, T, r)

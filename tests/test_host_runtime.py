@@ -87,3 +87,29 @@ result([live, waited, refused, after, H.fake_live()])
     assert max(live[6:8]) == 2 and live[8:] == [2] * 92   # ... but not under capture, nor the graph's
     assert all(waited)
     assert refused == -2 and after == 0 and end == 0
+
+
+def test_kde_launches_cover_narrow_images_and_few_frames(tmp_path):
+    """An image's tiles pad its rows by little more than threads of four pixels
+    must, whatever its width; a small image's window rows are split over more
+    waves even if there is one frame of them."""
+    r = fake_hip.run(tmp_path, """
+import re
+out = []
+sigma = (ctypes.c_float * 3)(6, 6, 6)
+for h, w, T, rad in ((100000, 1, 2, 1), (100000, 3, 2, 1), (60000, 8, 2, 2), (62500, 16, 2, 1), (30000, 33, 2, 2),
+                     (15384, 65, 16, 2), (14000, 97, 2, 2), (7692, 130, 16, 2), (7000, 200, 4, 2), (1080, 1920, 16, 2),
+                     (288, 352, 1, 32), (288, 352, 1, 5), (480, 640, 1, 12)):
+    log()
+    assert L.pwl_kde(None, 2, A, A, h, w, T, rad, sigma, A, None) == 0
+    (c,) = [c for c in log() if c[0] == "launch"]
+    S = int(re.search(r"k_kdeILin?[0-9]+ELi([124])EE", c[1]).group(1))
+    out.append((h, w, T, S, int(c[2]) * int(c[3]) * int(c[4]) // S))
+result(out)
+""")
+    for H, W, T, S, threads in r:
+        least = H * ((W + 3) // 4)
+        assert threads >= least
+        assert threads <= 1.17 * least + 1024, (H, W)      # an eighth or a seventh, and the last rows
+        if T == 1:
+            assert S == 4, (H, W, S)
