@@ -309,7 +309,7 @@ pwl_status pwl_locate(const pwl_table* t, const float* x, int32_t* seg, int64_t 
  * workgroup also sums every point's hat weights into one FP64 dL/dv region
  * per table in LDS and stores each region, rounded to FP32, as that unit's
  * N + 1 partial sums of the table in a buffer the batch owns; a second kernel
- * adds each table's partial sums in slice order in FP64.
+ * adds each table's partial sums in a fixed order in FP64.
  * Packs the copies, uploads the plan and synchronises `stream`.
  */
 pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int64_t* offsets, void* stream,

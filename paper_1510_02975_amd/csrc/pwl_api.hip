@@ -1021,6 +1021,7 @@ pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int
   size_t nparts = 0;
   for (const pwl::BatchGroup& g : plans[1].groups)
     for (int q = g.r0; q < g.r1; ++q, ++nparts) ++tab_first[plans[1].runs[q].table + 1];
+  const int32_t max_parts = *std::max_element(tab_first.begin(), tab_first.end());
   for (int i = 0; i < T; ++i) tab_first[i + 1] += tab_first[i];
   std::vector<int64_t> tab_part(std::max<size_t>(1, nparts));
   {
@@ -1120,6 +1121,7 @@ pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int
   bt->bl.dv_len = tab_dv[T];
   bt->bl.T = T;
   bt->bl.max_n = *std::max_element(Ns.begin(), Ns.end());
+  bt->bl.max_parts = max_parts;
   bt->bl.part = reinterpret_cast<float*>(b + o_part);
   bt->bl.tab_part = reinterpret_cast<const int64_t*>(b + o_tpart);
   bt->bl.tab_first = reinterpret_cast<const int32_t*>(b + o_tfirst);

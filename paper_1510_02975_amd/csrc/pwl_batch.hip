@@ -27,7 +27,7 @@
 // dL/dv region per table of the unit in LDS after the images.  After the
 // unit the workgroup stores every region, rounded to FP32, as that run's
 // partial sums in a buffer of the batch; k_batch_dv_reduce then adds each
-// table's partial sums in slice order, in FP64, so dL/dv does not depend on
+// table's partial sums in a fixed order, in FP64, so dL/dv does not depend on
 // the order in which the workgroups ran.
 #include <hip/hip_runtime.h>
 
@@ -376,32 +376,57 @@ __global__ __launch_bounds__(1024) void k_batch_bwd(const BatchRun* __restrict__
   }
 }
 
-// dL/dv of table blockIdx.x, entries 256 blockIdx.y + threadIdx.x: each the
-// sum, in FP64 and in slice order (a fixed order: the result does not depend
-// on how the workgroups ran), of its runs' partial sums; zero for a table
-// without points.  Writes every entry of dv.
-__global__ __launch_bounds__(256) void k_batch_dv_reduce(const float* __restrict__ part,
-                                                         const int64_t* __restrict__ tab_part,
-                                                         const int32_t* __restrict__ tab_first,
-                                                         const int64_t* __restrict__ tab_dv,
-                                                         float* __restrict__ dv) {
-  const int t = blockIdx.x;
+// dL/dv of table blockIdx.x, entries 256 blockIdx.y + threadIdx.x mod 256:
+// each the sum, in FP64 and in a fixed order (the result does not depend on
+// how the workgroups ran), of its runs' partial sums; zero for a table without
+// points.  Writes every entry of dv.  The list of a table's runs is a chain of
+// loads and additions, so where a few tables have most of the points it is
+// summed in P consecutive parts, by as many groups of 256 threads, and those
+// sums added in order.
+constexpr int kReduceEntries = 256;
+constexpr int kReduceParts = 4;
+template <int P>
+__global__ __launch_bounds__(kReduceEntries* P) void k_batch_dv_reduce(const float* __restrict__ part,
+                                                                      const int64_t* __restrict__ tab_part,
+                                                                      const int32_t* __restrict__ tab_first,
+                                                                      const int64_t* __restrict__ tab_dv,
+                                                                      float* __restrict__ dv) {
+  __shared__ double s_sum[P > 1 ? P : 1][kReduceEntries];
+  const int t = blockIdx.x, e = threadIdx.x % kReduceEntries, p = wave_first() / kReduceEntries;
   const int64_t d0 = tab_dv[t], n1 = tab_dv[t + 1] - d0;
-  const int j0 = tab_first[t], j1 = tab_first[t + 1];
-  const int64_t k = (int64_t)blockIdx.y * blockDim.x + threadIdx.x;
+  const int64_t k = (int64_t)blockIdx.y * kReduceEntries + e;
+  if ((int64_t)blockIdx.y * kReduceEntries >= n1) return;   // the whole workgroup
+  const int first = tab_first[t];
+  const int64_t n = tab_first[t + 1] - first;
+  const int j0 = first + (int)(n * p / P), j1 = first + (int)(n * (p + 1) / P);
+  double acc = 0.0;
   if (k < n1) {
-    double acc = 0.0;
+    // loads in flight together, added in order; the rest in fours, from a
+    // clamped index, so that they need not wait for each other either
+    constexpr int kInFlight = P > 1 ? 16 : 8;
     int j = j0;
-    for (; j + 8 <= j1; j += 8) {   // eight loads in flight, added in order
-      float v[8];
+    for (; j + kInFlight <= j1; j += kInFlight) {
+      float v[kInFlight];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = part[tab_part[j + q] + k];
+      for (int q = 0; q < kInFlight; ++q) v[q] = part[tab_part[j + q] + k];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) acc += (double)v[q];
+      for (int q = 0; q < kInFlight; ++q) acc += (double)v[q];
     }
-    for (; j < j1; ++j) acc += (double)part[tab_part[j] + k];
-    dv[d0 + k] = (float)acc;
+    for (; j < j1; j += 4) {
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = part[tab_part[min(j + q, j1 - 1)] + k];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc += j + q < j1 ? (double)v[q] : 0.0;
+    }
   }
+  if constexpr (P > 1) {
+    s_sum[p][e] = acc;
+    __syncthreads();
+    if (p != 0) return;
+    for (int q = 1; q < P; ++q) acc += s_sum[q][e];
+  }
+  if (k < n1) dv[d0 + k] = (float)acc;
 }
 
 // One workgroup per table: its image and its deepest map cell.
@@ -455,8 +480,18 @@ hipError_t launch_batch(const BatchLaunch& bl, const float* x, const float* g, f
   const int v = vec ? 1 : 0;
   const hipError_t e = launch_plan(bl, backward ? bl.bwd : bl.fwd, x, g, y, dx, v, s);
   if (e != hipSuccess || !backward) return e;
-  hipLaunchKernelGGL(k_batch_dv_reduce, dim3((unsigned)bl.T, (unsigned)((bl.max_n + 256) / 256)), dim3(256), 0, s,
-                     bl.part, bl.tab_part, bl.tab_first, bl.tab_dv, dv);
+  // Lists of more than 32 partial sums in parts, unless that would make many
+  // large workgroups, most of them for short lists.  Fused backward, whole
+  // lists -> in parts: one table of N = 1024, 2^25 points (512 sums) 139 -> 125
+  // us, 2^20 (128) 23.4 -> 13.6; 4 tables 2^22 (64) 22.8 -> 20.5; 16 tables
+  // 2^22 (16) 20.2 -> 20.4; 512 tables 2^25 (2) 123 -> 128.
+  const unsigned ny = (unsigned)((bl.max_n + kReduceEntries) / kReduceEntries);
+  if (bl.max_parts > 32 && (int64_t)bl.T * ny <= 8192)
+    hipLaunchKernelGGL(k_batch_dv_reduce<kReduceParts>, dim3((unsigned)bl.T, ny), dim3(kReduceEntries * kReduceParts),
+                       0, s, bl.part, bl.tab_part, bl.tab_first, bl.tab_dv, dv);
+  else
+    hipLaunchKernelGGL(k_batch_dv_reduce<1>, dim3((unsigned)bl.T, ny), dim3(kReduceEntries), 0, s, bl.part, bl.tab_part,
+                       bl.tab_first, bl.tab_dv, dv);
   return hipGetLastError();
 }
 

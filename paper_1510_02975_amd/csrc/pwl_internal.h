@@ -216,6 +216,7 @@ struct BatchLaunch {
   int64_t dv_len;            // sum over tables of N + 1
   int32_t T;
   int32_t max_n;             // the largest table's N
+  int32_t max_parts;         // the backward's runs of the table with most of them
   float* part;               // device: every backward run's N + 1 partial dL/dv sums
   const int64_t* tab_part;   // device: per table, in table order, its runs' offsets into part in slice order
   const int32_t* tab_first;  // device [T + 1]: table t's entries of tab_part are [tab_first[t], tab_first[t+1])

@@ -363,3 +363,34 @@ def test_batch_units_cut_inside_runs(total):
         bt.free()
     for t in tabs:
         t.free()
+
+
+@pytest.mark.parametrize("N", [1, 255, 256, 600])
+@pytest.mark.parametrize("units", [1, 3, 8, 32, 33, 36, 65, 67, 131, 515])
+def test_batch_dv_of_many_units(units, N):
+    """dL/dv summed from few and from many units of one table (up to 32 in one
+    part, more in four, with remainders of each), and of a table beside it
+    with two units, against the oracle.  Units of 1024 points."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    t = P.pwl_build(O.GAUSSIAN, (1.0, 1.0), -5.0, 5.0, N, O.UNIFORM, O.INTERP)
+    u = P.pwl_build(O.BESSEL_J0, (1.0,), 0.0, 50.0, 40, O.UNIFORM, O.INTERP)
+    n = 1024 * units - 5
+    offs = [0, n, n + 1029]
+    xh, gh = W.uniform_points(-5.5, 5.5, offs[2], N), W.upstream_grad(offs[2], units)
+    xh[n:] = np.abs(xh[n:]) * 10.0
+    say("units %d, N=%d" % (units, N))
+    with launch_shape(P, P.KERNEL_BATCH_BACKWARD, (1, 64, 32)):
+        bt = P.pwl_batch_create([t, u], offs)
+    _, _, dv = P.pwl_batch_eval_backward(bt, torch.from_numpy(xh).to(dev), torch.from_numpy(gh).to(dev), want=())
+    dv = dv.cpu().numpy()
+    for i, tab in enumerate((t, u)):
+        d = P.pwl_table_download(tab)
+        X, xs, gs = (a.astype(np.float64) for a in (d["knots"], xh[offs[i]:offs[i + 1]], gh[offs[i]:offs[i + 1]]))
+        _, _, dvr = O.evaluate_backward(X, d["values"].astype(np.float64), xs, gs)
+        _, _, wk = O.evaluate_backward(X, np.zeros(len(X)), xs, np.abs(gs))
+        assert np.all(np.abs(dv[bt.dv_offsets[i]:bt.dv_offsets[i + 1]] - dvr) <= GRAD_TOL * wk + 1e-30), i
+    bt.free()
+    t.free()
+    u.free()

@@ -113,3 +113,24 @@ result(out)
         assert threads <= 1.17 * least + 1024, (H, W)      # an eighth or a seventh, and the last rows
         if T == 1:
             assert S == 4, (H, W, S)
+
+
+def test_batched_dv_of_few_tables_is_no_long_chain(tmp_path):
+    """However many units a table's points are cut into, a thread of the second
+    kernel adds no more of its partial sums than when a unit was a whole slice
+    of 65536 points (or 64, a few rounds of loads)."""
+    r = fake_hip.run(tmp_path, """
+out = []
+for T in (1, 2, 4, 16):
+    tabs = [build(1024) for _ in range(T)]
+    for total in (1 << 20, 10000000, 1 << 25, 45000000):
+        b = batch(tabs, [total * k // T for k in range(T + 1)])
+        log()
+        assert L.pwl_batch_eval_backward(b, A, A, A, A, A, None) == 0
+        k, red = [c for c in log() if c[0] == "launch"]
+        out.append([T, total, int(k[2]), int(red[4]) // 256])
+        L.pwl_batch_free(b)
+result(out)
+""")
+    for T, total, units, parts in r:
+        assert units // (T * parts) <= max(64, total // 65536 // T + 1), (T, total, units, parts)
