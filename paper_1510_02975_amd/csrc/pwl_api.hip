@@ -872,29 +872,63 @@ ClassPlan plan_slices(const int64_t* offsets, int T, const std::vector<int64_t>&
 }
 
 // Points per work unit: the slice, or half of it again and again down to
-// 2048, whichever costs least by a model of the launch: a unit costs its
-// points and a fixed part (staging, barriers, filling and draining the
-// loads; 0.3 of a vector iteration forward, 0.44 backward), and u units on C
-// CUs take u / C rounds and on average 0.6 of one more, or a little over one
-// round if there are no more units than CUs.  A launch of few slices thus
-// spreads over the chip, and one of a few rounds loses less to its last.
-// Measured in us, whole slices -> the chosen length: forward 64 tables,
-// 10^5 points 11.2 -> 7.1 (2048; 4096 7.2, 8192 9.5), 2^20 13.9 -> 6.6 (4096;
-// 2048 7.8, 8192 7.8), 300 tables 2^22 17.6 -> 15.0 (8192), 2^24 33.7 (32768,
-// the whole slice; 16384 37.4); fused backward 64 tables 2^20 54.2 -> 16.6
-// (4096), 300 tables 2^24 97.4 -> 77.6 (32768; 16384 85.2), 512 tables 2^25
-// 150.6 -> 133.7 (32768; 16384 143.0).
-int64_t unit_length(const ClassPlan& p, int64_t slice, int64_t iteration, int num_cu, bool backward) {
-  const double fixed = (backward ? 0.44 : 0.3) * (double)iteration;
-  int64_t best = slice;
+// 2048, whichever costs least by a model of the launch: a unit costs the
+// points of the longest one, a fixed part (barriers, filling and draining the
+// loads: 0.3 of a vector iteration) and 0.7 points per 16-byte word that it
+// stages, zeroes or stores; u units on C CUs take between u / C rounds and
+// the whole number above it, half way, and on average 0.45 of one more, or a
+// little over one round if there are no more units than CUs.  A launch of few
+// slices thus spreads over the chip, and one of a few rounds loses less to its
+// last, but tables whose images take as long as their points keep long units.
+// Past 8 rounds shorter units never pay.  Measured in us, whole slices -> the
+// chosen length: forward 64 tables, 10^5 points 11.2 -> 7.1 (2048; 4096 7.2,
+// 8192 9.5), 2^20 13.9 -> 6.6 (4096; 2048 7.8, 8192 7.8), 300 tables 2^22
+// 17.6 -> 15.0 (8192), 2^24 33.7 (32768, the whole slice; 16384 37.4); fused
+// backward 64 tables 2^20 54.2 -> 16.6 (4096), 300 tables 2^24 97.4 -> 77.6
+// (32768; 16384 85.2), 512 tables 2^25 150.6 -> 133.7 (32768; 16384 143.0);
+// 512 tables of N = 4096, 10^7 points 68.5 whole (16384 74.4; 8192 79.4), of
+// N = 16 41.2 (16384; whole 47.0).
+struct UnitLength {
+  int64_t len;       // points of a unit, at most
+  int64_t longest;   // of the longest one
+};
+UnitLength unit_length(const ClassPlan& p, const std::vector<int32_t>& nvec, const std::vector<int32_t>& Ns,
+                       int64_t slice, int64_t iteration, int num_cu, bool backward) {
+  // the lengths are slice, slice / 2, ..., slice / 2^halvings; everything lies
+  // between two multiples of the slice, so its pieces are counted in units of
+  // the shortest
+  constexpr int kMaxHalvings = 8;
+  int halvings = 0;
+  while (halvings < kMaxHalvings && (slice >> halvings) % 2 == 0 && (slice >> (halvings + 1)) >= 2048) ++halvings;
+  if ((int64_t)p.groups.size() > 8 * (int64_t)num_cu) halvings = 0;
+  const uint32_t shortest = (uint32_t)(slice >> halvings);
+  int64_t units[kMaxHalvings + 1] = {}, words[kMaxHalvings + 1] = {}, longest[kMaxHalvings + 1] = {};
+  for (const pwl::BatchGroup& g : p.groups) {
+    const uint32_t b = (uint32_t)(g.begin % slice), e = b + (uint32_t)(g.end - g.begin);
+    const uint32_t first = b / shortest, last = (e - 1) / shortest;
+    for (int h = 0; h <= halvings; ++h) {   // pieces of shortest * 2^h points
+      const uint32_t i0 = first >> h, n = (last >> h) - i0 + 1, len = shortest << h, cut = (i0 + 1) * len;
+      units[h] += n;
+      const uint32_t most = n == 1 ? e - b : (n == 2 ? std::max(cut - b, e - cut) : len);
+      longest[h] = std::max<int64_t>(longest[h], most);
+    }
+  }
+  if (halvings == 0 || p.groups.empty()) return UnitLength{slice, longest[0]};
+  for (const pwl::BatchRun& r : p.runs) {
+    const uint32_t b = (uint32_t)(r.begin % slice), e = b + (uint32_t)(r.end - r.begin);
+    const uint32_t first = b / shortest, last = (e - 1) / shortest;
+    const int64_t w = nvec[r.table] + (backward ? 2 * (int64_t)pwl::batch_dv_words(Ns[r.table]) : 0);
+    for (int h = 0; h <= halvings; ++h) words[h] += w * ((last >> h) - (first >> h) + 1);
+  }
+  const double fixed = 0.3 * (double)iteration;
+  UnitLength best{slice, longest[halvings]};
   double least = 0.0;
-  for (int64_t len = slice; len == slice || len >= 2048; len /= 2) {
-    int64_t units = 0;
-    for (const pwl::BatchGroup& g : p.groups) units += (g.end - 1) / len - g.begin / len + 1;
-    const double rounds = units > num_cu ? (double)units / num_cu + 0.6 : 1.2;
-    const double cost = rounds * (fixed + (double)len);
-    if (len == slice || cost < least) {
-      best = len;
+  for (int h = halvings; h >= 0; --h) {
+    const double u = (double)units[h], f = u / num_cu;
+    const double rounds = units[h] > num_cu ? 0.5 * (f + std::ceil(f)) + 0.45 : 1.15;
+    const double cost = rounds * (fixed + 0.7 * (double)words[h] / u + (double)longest[h]);
+    if (h == halvings || cost < 0.99 * least) {   // (longer units leave fewer partial sums)
+      best = UnitLength{(int64_t)shortest << h, longest[h]};
       least = cost;
     }
   }
@@ -1004,11 +1038,15 @@ pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int
     unrolls[dir] = cfg[dir].unroll;
     const int64_t slice = (int64_t)kSliceIterations[dir] * 4 * cfg[dir].block * cfg[dir].unroll;
     plans[dir] = plan_slices(offsets, T, img_word, nvec, Ns, dir == 1, slice, cap);
-    const int64_t len = unit_length(plans[dir], slice, slice / kSliceIterations[dir], num_cu, dir == 1);
-    // an iteration no longer than a unit: fewer vectors per thread, then fewer threads
-    while (4 * (int64_t)blocks[dir] * unrolls[dir] > len && unrolls[dir] > 1) unrolls[dir] /= 2;
-    while (4 * (int64_t)blocks[dir] * unrolls[dir] > len && blocks[dir] > 256 && blocks[dir] % 128 == 0) blocks[dir] /= 2;
-    cut_groups(&plans[dir], img_word, nvec, Ns, dir == 1, len);
+    const UnitLength ul =
+        unit_length(plans[dir], nvec, Ns, slice, slice / kSliceIterations[dir], num_cu, dir == 1);
+    // an iteration no longer than a unit: fewer vectors per thread, then, where
+    // slices are cut, fewer threads (512 tables of N = 4096 and 256 points
+    // each, which their workgroups mostly copy: 12.9 us, 14.9 in 512 threads)
+    while (4 * (int64_t)blocks[dir] * unrolls[dir] > ul.longest && unrolls[dir] > 1) unrolls[dir] /= 2;
+    while (4 * (int64_t)blocks[dir] * unrolls[dir] > ul.len && blocks[dir] > 256 && blocks[dir] % 128 == 0)
+      blocks[dir] /= 2;
+    cut_groups(&plans[dir], img_word, nvec, Ns, dir == 1, ul.len);
     const int64_t ng = (int64_t)plans[dir].groups.size();
     grids[dir] = (int)std::max<int64_t>(1, std::min<int64_t>(ng, (int64_t)num_cu * std::max(1, cfg[dir].wg_per_cu)));
   }

@@ -401,8 +401,8 @@ __global__ __launch_bounds__(kReduceEntries* P) void k_batch_dv_reduce(const flo
   const int j0 = first + (int)(n * p / P), j1 = first + (int)(n * (p + 1) / P);
   double acc = 0.0;
   if (k < n1) {
-    // loads in flight together, added in order; the rest in fours, from a
-    // clamped index, so that they need not wait for each other either
+    // loads in flight together, added in order; the rest in fours and the last
+    // few at once, so that they need not wait for each other either
     constexpr int kInFlight = P > 1 ? 16 : 8;
     int j = j0;
     for (; j + kInFlight <= j1; j += kInFlight) {
@@ -412,13 +412,19 @@ __global__ __launch_bounds__(kReduceEntries* P) void k_batch_dv_reduce(const flo
 #pragma unroll
       for (int q = 0; q < kInFlight; ++q) acc += (double)v[q];
     }
-    for (; j < j1; j += 4) {
+    for (; j + 4 <= j1; j += 4) {
       float v[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = part[tab_part[min(j + q, j1 - 1)] + k];
+      for (int q = 0; q < 4; ++q) v[q] = part[tab_part[j + q] + k];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc += j + q < j1 ? (double)v[q] : 0.0;
+      for (int q = 0; q < 4; ++q) acc += (double)v[q];
     }
+    float v[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (j + q < j1) v[q] = part[tab_part[j + q] + k];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) acc += (double)v[q];
   }
   if constexpr (P > 1) {
     s_sum[p][e] = acc;

@@ -134,3 +134,29 @@ result(out)
 """)
     for T, total, units, parts in r:
         assert units // (T * parts) <= max(64, total // 65536 // T + 1), (T, total, units, parts)
+
+
+def test_batch_units_of_large_tables_stay_long(tmp_path):
+    """Units are cut short for small tables, where a launch has few of them, but
+    not for tables whose images take as long to copy as a short unit's points;
+    and a unit per table that needs no cutting keeps the full workgroup."""
+    r = fake_hip.run(tmp_path, """
+out = []
+for N, T, total in ((4096, 512, 10000000), (4096, 512, 45000000), (4096, 64, 45000000), (4096, 512, 131072),
+                    (16, 512, 10000000), (64, 64, 100003)):
+    tabs = [build(N) for _ in range(T)]
+    b = batch(tabs, [total * k // T for k in range(T + 1)])
+    log()
+    assert L.pwl_batch_eval(b, A, A, None) == 0
+    assert L.pwl_batch_eval_backward(b, A, A, A, A, A, None) == 0
+    fwd, bwd, _ = [c for c in log() if c[0] == "launch"]
+    out.append([int(fwd[2]), int(fwd[4]), int(bwd[2]), int(bwd[4])])
+    L.pwl_batch_free(b)
+    for t in tabs:
+        L.pwl_table_free(t)
+result(out)
+""")
+    (_, _, a, _), (_, _, b, _), (_, _, c, _), (_, threads, _, bthreads), (_, _, d, _), (e, _, f, _) = r
+    assert a <= 664 and b <= 1885 and c <= 750   # slices of 65536, 32768 and 65536 points, split at the tables
+    assert threads == 1024 and bthreads == 1024
+    assert d >= 512 and e >= 40 and f >= 40
