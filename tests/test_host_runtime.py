@@ -160,3 +160,15 @@ result(out)
     assert a <= 664 and b <= 1885 and c <= 750   # slices of 65536, 32768 and 65536 points, split at the tables
     assert threads == 1024 and bthreads == 1024
     assert d >= 512 and e >= 40 and f >= 40
+
+
+def test_batch_creation_uploads_at_once(tmp_path):
+    """Creating a batch copies the tables' descriptors, their deepest cells and
+    everything else in one copy each, however many lists the plan has."""
+    r = fake_hip.run(tmp_path, """
+tabs = [build(n) for n in (16, 300, 4096)]
+log()
+b = batch(tabs, [0, 1 << 20, 1 << 22, 1 << 24])
+result([c[0] for c in log()])
+""")
+    assert r.count("copy") == 3 and r.count("malloc") == 1 and r.count("launch") == 1
