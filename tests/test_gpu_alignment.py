@@ -149,3 +149,67 @@ def test_staging_sizes_of_other_records(N, layout):
                 ref = O.evaluate(X, v.astype(np.float64), xh.astype(np.float64))
                 assert np.max(np.abs(got.cpu().numpy() - ref)) <= Y_TOL * max(1.0, np.max(np.abs(v)))
     t.free()
+
+
+@pytest.mark.parametrize("layout", ["packed", "soa", "pairs"])
+@pytest.mark.parametrize("N", [1023, 1024, 1025, 2047, 2048, 3071, 3072, 3073, 4096])
+def test_staging_in_full_workgroups(N, layout):
+    """The same thresholds in the 1024-thread workgroups of large launches
+    (more than one and a half of them per compute unit): a section's first
+    word per thread, its further words and the copied rest of a map of 8 N
+    cells, up to three records per thread and past them.  Bit for bit what
+    small launches of 256 threads give for the same points, with the table's
+    values and with given ones."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    n = cus * 1024 * 4 * 4 * 3 // 2 + 4 * 1024 + 3
+    t = P.pwl_build(O.LORENTZIAN, (1.0, 1.0), -20.0, 20.0, N, O.OPTIMAL, O.INTERP)
+    assert t.info()[5] == (8 * N if N <= 2048 else 4 * N)
+    d = P.pwl_table_download(t)
+    x = torch.empty(n, device=dev).uniform_(-21.0, 21.0, generator=torch.Generator(device=dev).manual_seed(N))
+    x[:N + 1] = torch.from_numpy(d["knots"]).to(dev)
+    vo = torch.from_numpy((1.0 + 0.5 * np.cos(np.arange(N + 1))).astype(np.float32)).to(dev)
+    say("full workgroups N=%d %s n=%d" % (N, layout, n))
+    with records_layout(P, {"packed": P.RECORDS_PACKED, "soa": P.RECORDS_SOA, "pairs": P.RECORDS_PAIRS}[layout]):
+        with launch_shape(P, P.KERNEL_FORWARD, (4, 1024, 32)):
+            y, yo = P.pwl_eval(t, x), P.pwl_eval(t, x, v_override=vo)
+        with launch_shape(P, P.KERNEL_FORWARD, (1, 256, 32)):
+            step = 50000
+            for b in range(0, n, step):
+                xs = x[b:b + step]
+                assert torch.equal(y[b:b + step], P.pwl_eval(t, xs)), b
+                assert torch.equal(yo[b:b + step], P.pwl_eval(t, xs, v_override=vo)), b
+    t.free()
+
+
+@pytest.mark.parametrize("N", [300, 1024, 2048, 4096])
+@pytest.mark.parametrize("shape", [(2, 768, 1), (4, 1024, 1), (2, 1024, 2)], ids=["2x768", "4x1024", "2x1024"])
+def test_backward_in_full_workgroups(N, shape):
+    """The fused backward past its small launches: y and dx bit for bit, and
+    dL/dv within the gradients' bound, what calls on pieces of the points give."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    n = cus * shape[1] * shape[0] * 4 + 4099
+    t = P.pwl_build(O.LORENTZIAN, (1.0, 1.0), -20.0, 20.0, N, O.OPTIMAL, O.PROJ)
+    gen = torch.Generator(device=dev).manual_seed(N)
+    x = torch.empty(n, device=dev).uniform_(-21.0, 21.0, generator=gen)
+    g = torch.empty(n, device=dev).normal_(generator=gen)
+    vo = torch.from_numpy((1.0 + 0.5 * np.cos(np.arange(N + 1))).astype(np.float32)).to(dev)
+    say("full backward workgroups N=%d shape %s n=%d" % (N, shape, n))
+    for v in (None, vo):
+        with launch_shape(P, P.KERNEL_BACKWARD, shape):
+            y, dx, dv = P.pwl_eval_backward(t, x, g, v_override=v)
+        want, weight = (torch.zeros(N + 1, dtype=torch.float64, device=dev) for _ in range(2))
+        step = 100000
+        for b in range(0, n, step):
+            xs, gs = x[b:b + step], g[b:b + step]
+            ys, dxs, dvs = P.pwl_eval_backward(t, xs, gs, v_override=v)
+            assert torch.equal(y[b:b + step], ys) and torch.equal(dx[b:b + step], dxs), b
+            want += dvs
+            weight += P.pwl_eval_backward(t, xs, gs.abs(), v_override=v, want=("dv",))[2]
+        assert torch.all((dv - want).abs() <= GRAD_TOL * weight + 1e-30)
+    t.free()

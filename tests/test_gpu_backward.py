@@ -204,3 +204,26 @@ def test_workspace_taken_under_capture(before):
         assert torch.equal(a, b)
     t.free()
     ref.free()
+
+
+def test_workspace_grows_with_the_points():
+    """One table at increasing numbers of points, each needing more workgroups'
+    rows than the call before: dL/dv against the oracle at every step, then
+    back at the first, with the same bits."""
+    import paper_1510_02975_amd as P
+    library()
+    dev = device()
+    t = P.pwl_build(O.GAUSSIAN, (1.0, 1.0), -5.0, 5.0, 512, O.OPTIMAL, O.PROJ)
+    d = P.pwl_table_download(t)
+    X, v = d["knots"].astype(np.float64), d["values"].astype(np.float64)
+    x_h, g_h = W.grad_inputs(1 << 21)
+    x, g = torch.from_numpy(x_h).to(dev), torch.from_numpy(g_h).to(dev)
+    first = None
+    for n in (1024, 8192, 65536, 1 << 18, 1 << 21, 8192, 1024):
+        _, _, dv = P.pwl_eval_backward(t, x[:n], g[:n])
+        x64, g64 = x_h[:n].astype(np.float64), g_h[:n].astype(np.float64)
+        _, _, dvr = O.evaluate_backward(X, v, x64, g64)
+        assert np.all(np.abs(dv.cpu().numpy() - dvr) <= GRAD_TOL * _abs_weight(X, x64, g64) + 1e-30), n
+        first = dv if first is None else first
+    assert torch.equal(dv, first)
+    t.free()

@@ -172,3 +172,30 @@ b = batch(tabs, [0, 1 << 20, 1 << 22, 1 << 24])
 result([c[0] for c in log()])
 """)
     assert r.count("copy") == 3 and r.count("malloc") == 1 and r.count("launch") == 1
+
+
+def test_large_launches_have_full_workgroups(tmp_path):
+    """The sizes the GPU tests of the staging take: 1024 threads of four vectors
+    past one and a half workgroups per compute unit forward, the tuned shape past
+    one backward, and 256 threads of one vector for small launches."""
+    r = fake_hip.run(tmp_path, """
+out = []
+L.pwl_set_launch.argtypes = [i32] * 4
+for N in (300, 1024, 4096):
+    t = build(N)
+    for shape, n in (((4, 1024, 32), 256 * 1024 * 4 * 4 * 3 // 2 + 4099), ((1, 256, 32), 50000)):
+        assert L.pwl_set_launch(0, *shape) == 0
+        log()
+        assert L.pwl_eval(t, None, A, A, n, None) == 0
+        c = log()[0]
+        out.append([c[1], int(c[4]), shape])
+    for shape in ((2, 768, 1), (4, 1024, 1)):
+        assert L.pwl_set_launch(1, *shape) == 0
+        log()
+        assert backward(t, 256 * shape[1] * shape[0] * 4 + 4099) == 0
+        c = [c for c in log() if c[0] == "launch"][0]
+        out.append([c[1], int(c[4]), shape])
+result(out)
+""")
+    for name, threads, (unroll, block, _) in r:
+        assert threads == block and "ILi%dE" % unroll in name, (name, threads)
