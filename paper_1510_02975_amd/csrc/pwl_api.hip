@@ -1121,7 +1121,6 @@ pwl_status pwl_batch_create(const pwl_table* const* tables, int32_t T, const int
       ClassPlan& p = plans[dir];
       for (pwl::BatchRun& r : p.runs) {
         const pwl_table* t = tables[r.table];
-        r.nvec = nvec[r.table];
         r.N = t->bp.N;
         r.K = t->bp.K;
         r.a32 = t->bp.a32;

@@ -13,7 +13,6 @@ namespace pwl {
 constexpr int kFineCellsPerSegment = 256;   // M = 256 N density cells
 constexpr int kDensityCellsPerBlock = 1024; // cells scanned by one build workgroup
 constexpr int kMaxDensityBlocks = kFineCellsPerSegment * PWL_MAX_N / kDensityCellsPerBlock;
-constexpr int kBuildThreads = 256;
 constexpr int kGaussPoints = 16;            // Gauss-Legendre nodes per segment for <f, phi_k>
 constexpr int kKnotPad = 8;                 // NaN sentinels after the last interior knot in LDS
 constexpr int kMaxUnrolledCount = 4;        // knots per map cell handled by unrolled compares
@@ -167,9 +166,10 @@ struct BatchRun {
   int32_t dv_lds;            // backward: word offset of the table's FP64 dL/dv among the slice's
   int64_t begin, end;
   int64_t part;              // backward: N + 1 summed over the runs before it
-  int32_t table, nvec, N, K;
+  int32_t table, N, K;
   float a32, b32, scale32;
   int32_t maxc;              // most knots sharing one map cell (the unrolled compare depth)
+  int32_t pad;
 };
 static_assert(sizeof(BatchRun) == 64, "BatchRun is 64 bytes");
 
@@ -203,7 +203,7 @@ struct BatchPlan {           // the work units of one launch
   BatchRun* runs;            // device
   BatchGroup* groups;        // device [ngroups]
   const float4* arena;       // device: the images, table 0 first
-  int32_t grid;              // workgroups launched (the forward's take groups grid apart, the backward's one each)
+  int32_t grid;              // workgroups launched, each taking groups `grid` apart (the backward's mostly one)
   int32_t ngroups;
   int32_t nruns;
   size_t lds;                // the largest group's LDS bytes

@@ -21,7 +21,6 @@ constexpr int kWaitVm0 = 0x0F70;   // s_waitcnt vmcnt(0), the other counters not
 // Packed records: one 16-byte word per segment (a segment's lookup is one
 // LDS read of 12 or 16 bytes).
 struct Smem {
-  static constexpr bool kRecords = true;   // looked up by record(segment)
   float4* rec;      // [N]           {x_k, v_k, slope_k, x_{k+1}}
   float* knot;      // [N + pad]     knot[0] = a, knot[k] = x_k for 1 <= k <= N-1, NaN from N on
   uint16_t* lo;     // [K + 1]       lo[u] = #{interior knots in cells < u}; lo[K] = N - 1
@@ -34,7 +33,6 @@ struct Smem {
 // the knot array (no compare reads its entry 0).  A lookup reads the three fields separately, 4 bytes each.  Forward
 // evaluation only.
 struct SmemSoA {
-  static constexpr bool kRecords = true;
   float* knot;      // [N + pad]  knot[0] = a, knot[k] = x_k for 1 <= k <= N-1, NaN from N on
   float* rv;        // [N] v_k
   float* rs;        // [N] slope_k
@@ -47,7 +45,6 @@ struct SmemSoA {
 // with the one before them (the segment's own knot among them; adjacent, so one paired
 // read for a cell of one knot) and one pair.  Forward evaluation only.
 struct SmemPairs {
-  static constexpr bool kRecords = false;
   float2* vs;       // [N]        {v_k, slope_k}
   float* knot;      // [N + pad]  knot[0] = a, knot[k] = x_k for 1 <= k <= N-1, NaN from N on
   uint16_t* lo;
