@@ -885,7 +885,7 @@ ClassPlan plan_slices(const int64_t* offsets, int T, const std::vector<int64_t>&
 // 8192 9.5), 2^20 13.9 -> 6.6 (4096; 2048 7.8, 8192 7.8), 300 tables 2^22
 // 17.6 -> 15.0 (8192), 2^24 33.7 (32768, the whole slice; 16384 37.4); fused
 // backward 64 tables 2^20 54.2 -> 16.6 (4096), 300 tables 2^24 97.4 -> 77.6
-// (32768; 16384 85.2), 512 tables 2^25 150.6 -> 133.7 (32768; 16384 143.0);
+// (32768; 16384 85.2), 512 tables 2^25 150.6 -> 129.3 (32768; 16384 138);
 // 512 tables of N = 4096, 10^7 points 68.5 whole (16384 74.4; 8192 79.4), of
 // N = 16 41.2 (16384; whole 47.0).
 struct UnitLength {

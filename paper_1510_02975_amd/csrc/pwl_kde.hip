@@ -109,13 +109,14 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
       at[j][2] = 4 * (255 + 2 * kListLen + (int)((p >> 16) & 255u));
     }
     // window rows [i0, i1): frame i / (2r+1), row i % (2r+1) - r of the window
-    const int w = 2 * r + 1;
-    const int64_t n = (int64_t)T * w, i0 = n * part / S, i1 = n * (part + 1) / S;
+    // (fewer than 2^30 of them where they are split)
+    const uint32_t w = R >= 0 ? 2 * R + 1 : 2 * (uint32_t)r + 1;
+    const uint32_t n = (uint32_t)T * w, i0 = n * part / S, i1 = n * (part + 1) / S;
     const int k0 = S > 1 ? (int)(i0 / w) : 0, k1 = S > 1 ? (int)((i1 + w - 1) / w) : T;
     for (int k = k0; k < k1; ++k) {
       const uint32_t* __restrict__ hk = hist + (int64_t)k * H * W;
-      const int dy0 = S > 1 && k == k0 ? (int)(i0 - (int64_t)k * w) - r : -r;
-      const int dy1 = S > 1 && k == k1 - 1 ? (int)(i1 - (int64_t)k * w) - r - 1 : r;   // the last row
+      const int dy0 = S > 1 && k == k0 ? (int)(i0 - k * w) - r : -r;
+      const int dy1 = S > 1 && k == k1 - 1 ? (int)(i1 - k * w) - r - 1 : r;   // the last row
       if constexpr (R >= 0) {
         // one row of the window at a time, the next row's loads in flight
         const bool inside = x0 >= R && x0 + kPx + R <= W;
@@ -169,17 +170,17 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
 template <int R>
 void launch_kde_r(const EvalTable& t, int mode, const uint32_t* f, const uint32_t* h, int H, int W, int T, int r,
                   float is0, float is1, float is2, float* out, int num_cu, hipStream_t s) {
-  // The widest tile that pads the rows by at most an eighth, since what a tile
+  // The widest tile that pads the rows by at most a sixth, since what a tile
   // has beyond the image is computed all the same; one lane along a row (whose
   // lanes each read a row of their own) only where two would pad a seventh more.
-  // 10^6 pixels of uniformly distributed bytes, 64-pixel tiles -> these, T = 16,
-  // r = 2: W = 1 4050 -> 850 us, 16 436 -> 222, 33 306 -> 250, 65 427 -> 233, 97
-  // 288 -> 231; T = 2, r = 1: W = 16 27 -> 14, 65 25 -> 18.  Wide images the same
-  // either way.
+  // About 10^6 pixels of uniformly distributed bytes, 64-pixel tiles -> these:
+  // T = 16, r = 2, W = 1 4972 -> 864 us, 16 446 -> 222, 33 308 -> 264, 65 442 ->
+  // 242, 97 303 -> 248, 200 278 -> 237; T = 2, r = 1, W = 16 27.2 -> 14.5, 65 25.4
+  // -> 20.0, but 130 17.0 -> 17.9.  From 330 pixels on it is the widest.
   int bits = kTileBits;
   auto columns = [&](int b) { return ((int64_t)W + (kPx << b) - 1) / (kPx << b); };
   auto padded = [&](int b) { return columns(b) * (kPx << b); };
-  while (bits > 0 && padded(bits) > (int64_t)W + W / 8) --bits;
+  while (bits > 0 && padded(bits) > (int64_t)W + W / 6) --bits;
   if (bits == 0 && 7 * padded(1) <= 8 * padded(0)) bits = 1;
   const int th = 64 >> bits;
   const unsigned gx = (unsigned)columns(bits);
@@ -199,9 +200,9 @@ void launch_kde_r(const EvalTable& t, int mode, const uint32_t* f, const uint32_
   // r = 2 227 -> 207; past it 1080 x 1920 439 (437 in 4 parts); fewer taps: 480 x
   // 640 T = 2, r = 2 17.6 -> 14.6, past it 720 x 1280 T = 1, r = 1 9.5 (12.4 in
   // 4 parts).
-  const int64_t taps = (int64_t)T * (2 * r + 1) * (2 * r + 1);
+  const int64_t rows_of_all = (int64_t)T * (2 * r + 1), taps = rows_of_all * (2 * r + 1);
   auto splits = [&](int S) {
-    return (int64_t)T * (2 * r + 1) >= S && tiles * S <= (int64_t)num_cu * (taps >= 100 * S ? 60 : 16);
+    return rows_of_all >= S && rows_of_all < (1 << 30) && tiles * S <= (int64_t)num_cu * (taps >= 100 * S ? 60 : 16);
   };
   if (splits(4))
     launch(k_kde<R, 4>, 4);

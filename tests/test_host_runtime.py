@@ -110,7 +110,7 @@ result(out)
     for H, W, T, S, threads in r:
         least = H * ((W + 3) // 4)
         assert threads >= least
-        assert threads <= 1.17 * least + 1024, (H, W)      # an eighth or a seventh, and the last rows
+        assert threads <= 1.17 * least + 1024, (H, W)      # a sixth, and the last rows
         if T == 1:
             assert S == 4, (H, W, S)
 
