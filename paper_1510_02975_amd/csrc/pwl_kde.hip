@@ -80,8 +80,9 @@ __device__ __forceinline__ float tap(const char* list, const int (&at)[3], int h
 
 // R >= 0: the window radius; -1: any radius, from r.  A wave's tile has 2^bits
 // lanes along a row and the others along y.  S waves of a workgroup share a
-// tile, each with its part of the T (2r+1) rows of the windows.
-template <int R, int S>
+// tile, each with its part of the reference frames or, where S does not divide
+// their number (ROWS), of the T (2r+1) rows of the windows.
+template <int R, int S, bool ROWS>
 __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, const uint32_t* __restrict__ frame,
                                                      const uint32_t* __restrict__ hist, int H, int W, int T,
                                                      int r, int bits, float is0, float is1, float is2,
@@ -108,15 +109,16 @@ __global__ __launch_bounds__(kKdeThreads) void k_kde(EvalTable t, int mode, cons
       at[j][1] = 4 * (255 + kListLen + (int)((p >> 8) & 255u));
       at[j][2] = 4 * (255 + 2 * kListLen + (int)((p >> 16) & 255u));
     }
-    // window rows [i0, i1): frame i / (2r+1), row i % (2r+1) - r of the window
-    // (fewer than 2^30 of them where they are split)
+    // ROWS: window rows [i0, i1) of fewer than 2^30, row i being row
+    // i % (2r+1) - r of the window in frame i / (2r+1)
     const uint32_t w = R >= 0 ? 2 * R + 1 : 2 * (uint32_t)r + 1;
     const uint32_t n = (uint32_t)T * w, i0 = n * part / S, i1 = n * (part + 1) / S;
-    const int k0 = S > 1 ? (int)(i0 / w) : 0, k1 = S > 1 ? (int)((i1 + w - 1) / w) : T;
+    const int k0 = ROWS ? (int)(i0 / w) : (int)((int64_t)T * part / S);
+    const int k1 = ROWS ? (int)((i1 + w - 1) / w) : (int)((int64_t)T * (part + 1) / S);
     for (int k = k0; k < k1; ++k) {
       const uint32_t* __restrict__ hk = hist + (int64_t)k * H * W;
-      const int dy0 = S > 1 && k == k0 ? (int)(i0 - k * w) - r : -r;
-      const int dy1 = S > 1 && k == k1 - 1 ? (int)(i1 - k * w) - r - 1 : r;   // the last row
+      const int dy0 = ROWS && k == k0 ? (int)(i0 - k * w) - r : -r;
+      const int dy1 = ROWS && k == k1 - 1 ? (int)(i1 - k * w) - r - 1 : r;   // the last row
       if constexpr (R >= 0) {
         // one row of the window at a time, the next row's loads in flight
         const bool inside = x0 >= R && x0 + kPx + R <= W;
@@ -191,8 +193,8 @@ void launch_kde_r(const EvalTable& t, int mode, const uint32_t* f, const uint32_
                        W, T, r, bits, is0, is1, is2, out);
   };
   // One wave per tile leaves a small image with few waves, and a mid-sized
-  // one with an uneven last round (24 waves fit a CU): the rows of all windows
-  // are then split over 2 or 4 waves.  With at least 100 taps per part (16
+  // one with an uneven last round (24 waves fit a CU): the frames, or the rows of
+  // all windows, are then split over 2 or 4 waves.  With at least 100 taps per part (16
   // frames, r = 2; one frame, r = 10) it pays up to 60 waves per CU, with fewer
   // up to 16.  One wave per tile -> the split chosen, uniformly distributed
   // bytes: 288 x 352 T = 16, r = 2 67 -> 32 us, T = 1, r = 32 1363 -> 378;
@@ -204,12 +206,13 @@ void launch_kde_r(const EvalTable& t, int mode, const uint32_t* f, const uint32_
   auto splits = [&](int S) {
     return rows_of_all >= S && rows_of_all < (1 << 30) && tiles * S <= (int64_t)num_cu * (taps >= 100 * S ? 60 : 16);
   };
-  if (splits(4))
-    launch(k_kde<R, 4>, 4);
-  else if (splits(2))
-    launch(k_kde<R, 2>, 2);
-  else
-    launch(k_kde<R, 1>, 1);
+  if (splits(4)) {
+    if (T % 4 == 0) launch(k_kde<R, 4, false>, 4); else launch(k_kde<R, 4, true>, 4);
+  } else if (splits(2)) {
+    if (T % 2 == 0) launch(k_kde<R, 2, false>, 2); else launch(k_kde<R, 2, true>, 2);
+  } else {
+    launch(k_kde<R, 1, false>, 1);
+  }
 }
 
 }  // namespace

@@ -103,7 +103,7 @@ for h, w, T, rad in ((100000, 1, 2, 1), (100000, 3, 2, 1), (60000, 8, 2, 2), (62
     log()
     assert L.pwl_kde(None, 2, A, A, h, w, T, rad, sigma, A, None) == 0
     (c,) = [c for c in log() if c[0] == "launch"]
-    S = int(re.search(r"k_kdeILin?[0-9]+ELi([124])EE", c[1]).group(1))
+    S = int(re.search(r"k_kdeILin?[0-9]+ELi([124])ELb[01]EE", c[1]).group(1))
     out.append((h, w, T, S, int(c[2]) * int(c[3]) * int(c[4]) // S))
 result(out)
 """)
